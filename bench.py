@@ -66,7 +66,8 @@ def algorithmic_bytes(M, K, N, symmetric=False):
 # device sources each kernel family is built from (the stored counter
 # summary of a kernel is valid while these files are unchanged)
 KERNEL_SOURCES = {
-    "linear": ("kernels.hip", "device_common.h", "qlin_internal.h"),
+    "linear": ("kernels.hip", "decode_common.h", "device_common.h", "qlin_internal.h"),
+    "mid": ("mid.hip", "decode_common.h", "device_common.h", "qlin_internal.h"),
     "tiled": ("tiled.hip", "device_common.h", "qlin_internal.h"),
     "attention": ("attn.hip", "attn_internal.h", "device_common.h", "qlin_internal.h"),
 }
@@ -75,6 +76,8 @@ KERNEL_SOURCES = {
 def kernel_family(kernel):
     if kernel.startswith("k_attn"):
         return "attention"
+    if kernel.startswith("k_mid"):
+        return "mid"
     return "tiled" if kernel.startswith("k_tiled") else "linear"
 
 

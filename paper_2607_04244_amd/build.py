@@ -15,10 +15,11 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqlin.so")
-# (source, extra flags).  tiled.hip and attn.hip keep matrix-core results in
-# VGPRs: their products feed vector instructions directly (dequantization,
+# (source, extra flags).  tiled.hip, mid.hip and attn.hip keep matrix-core results
+# in VGPRs: their products feed vector instructions directly (dequantization,
 # softmax rescaling), which would otherwise go through AGPR copies.
-SOURCES = [("kernels.hip", []), ("tiled.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]), ("attn.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
+SOURCES = [("kernels.hip", []), ("tiled.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
+           ("mid.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]), ("attn.hip", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
            ("qlin.cpp", []), ("attn_abi.cpp", [])]
 HOST_SOURCES = ("qlin.cpp", "attn_abi.cpp")       # no device code: plain C++ against the HIP headers
 LIB_ASAN = os.path.join(HERE, "libqlin_asan.so")

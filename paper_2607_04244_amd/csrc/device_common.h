@@ -12,6 +12,7 @@ typedef __attribute__((address_space(1))) void glb_void_t;   // global memory
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
@@ -52,28 +53,70 @@ __device__ inline uint16_t cvt_bf16(float v) {
 __device__ inline float bf16_lo_to_f32(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi_to_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// The four "128 + q" bf16 pairs of one packed word: pair i holds nibbles i
-// (low half) and i + 4 (high half).  Each pair is one v_and_or_b32; the two
-// constants live in registers (gfx9 VOP3 takes no literal), loaded once per
-// kernel by ExtractConsts.
-struct ExtractConsts {
+// Two exact routes turn a packed word into bf16 weights; a handle's scales
+// decide at creation which one its s|z words are stored for.
+//
+// F16 = true (every scale in [2^-25, 2^4)): the codes enter the dequantizing
+// product as f16 subnormals.  A nibble at bits 0-3 of a 16-bit half is the f16
+// number q 2^-24 and one at bits 4-7 is q 2^-20, so a word needs one shift and
+// four ANDs for its eight codes, and no exponent bits are OR-ed in.  The
+// matrix op takes f16 subnormals exactly (checked over 2 million products of
+// every code with scales across the range).  The scale is stored as
+// s 2^kF16Exp in f16 (8 significant bits: exact), divided by 16 in the columns
+// r >= 2 of a 4-column block, whose codes sit at bits 4-7.  All weights then
+// come out multiplied by 2^(kF16Exp - 24), exactly, so they round to the same
+// bf16 significands, and the sum is multiplied by kF16Unscale before its one
+// rounding.
+//
+// F16 = false (any scale in [2^-100, 2^100]): 0x4300 | q is the bf16 number
+// 128 + q: three shifts and four v_and_or_b32 per word.
+//
+// Measured per word (cycles a wave64 instruction holds a SIMD with 2 waves on
+// it): v_and_b32 of two VGPRs and v_lshrrev_b32 2.7, v_and_or_b32 4.6,
+// v_cvt_pk_bf16_f32 4.6, the 4x4x4 matrix op 8.2: 13.5 against 26.5 cycles of
+// extraction per eight weights.
+constexpr int kF16Exp = 12;
+constexpr float kF16Unscale = 4096.0f;     // 2^(24 - kF16Exp)
+
+struct Pairs { uint32_t a0, a1, a2, a3; };
+
+// Masks of the extraction; in registers (gfx9 VOP3 takes no literal, and an
+// AND with a scalar operand issues at half the rate of one with two vector
+// operands), opaque to the optimizer so that they stay there.
+template <bool F16>
+struct ExtractConsts;
+template <>
+struct ExtractConsts<false> {
     uint32_t mask, magic;
     __device__ inline ExtractConsts() {
-        // opaque to the optimizer, so the values stay in registers
         mask = __builtin_amdgcn_readfirstlane(0x000F000Fu);
         magic = 0x43004300u;                        // bf16 128.0 in both halves
         asm volatile("" : "+v"(magic));
     }
+    // the four "128 + q" bf16 pairs: pair i holds nibbles i (low half) and i + 4 (high half)
+    __device__ inline Pairs pairs(uint32_t P) const {
+        Pairs o;
+        o.a0 = (P & mask) | magic;
+        o.a1 = ((P >> 4) & mask) | magic;
+        o.a2 = ((P >> 8) & mask) | magic;
+        o.a3 = ((P >> 12) & mask) | magic;
+        return o;
+    }
 };
-struct Pairs { uint32_t a0, a1, a2, a3; };
-__device__ inline Pairs extract_pairs(uint32_t P, const ExtractConsts &k) {
-    Pairs o;
-    o.a0 = (P & k.mask) | k.magic;
-    o.a1 = ((P >> 4) & k.mask) | k.magic;
-    o.a2 = ((P >> 8) & k.mask) | k.magic;
-    o.a3 = ((P >> 12) & k.mask) | k.magic;
-    return o;
-}
+template <>
+struct ExtractConsts<true> {
+    uint32_t lo, hi;
+    __device__ inline ExtractConsts() {
+        lo = 0x000F000Fu;
+        hi = 0x00F000F0u;
+        asm volatile("" : "+v"(lo), "+v"(hi));
+    }
+    // the same four pairs as f16 q 2^-24 (a0, a2) and q 2^-20 (a1, a3)
+    __device__ inline Pairs pairs(uint32_t P) const {
+        const uint32_t p8 = P >> 8;
+        return Pairs{P & lo, P & hi, p8 & lo, p8 & hi};
+    }
+};
 
 // One lane's 16 bytes of a weight block.
 __device__ inline uint4 load_block(const uint4 *codes, size_t idx) { return codes[idx]; }
@@ -88,73 +131,113 @@ __device__ inline uint4 load_block_nt(const uint4 *codes, size_t idx) {
     return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const v4u *)codes + idx));
 }
 
-// Per (column, group) dequantization word: bf16 s in the low half and the
-// bf16 offset zc = -(128 + z) in the high half (exact: an integer of 8
-// significant bits), so that (128 + q) * s + zc * s = (q - z) * s.
-// Symmetric handles store only s (z = 8, zc = -136 = bf16 0xC308).
-constexpr uint32_t kZcSymmetric = 0xC308u;
-template <bool SYM>
-__device__ inline uint32_t load_sz(const void *sz, size_t idx) {
-    if constexpr (SYM) {
-        return (uint32_t)((const uint16_t *)sz)[idx] | (kZcSymmetric << 16);
-    } else {
-        return ((const uint32_t *)sz)[idx];
-    }
-}
+// Per (column, group) dequantization word of lane l's column n16 = l & 15 of a
+// tile.  What is stored, and loaded by load_sz:
+//   F16 = false, zero-points: bf16 s in the low half, bf16 zc = -(128 + z) in
+//     the high half (exact: an integer of 8 significant bits), so that
+//     (128 + q) * s + zc * s = (q - z) * s;
+//   F16 = true, zero-points: f16 s' (see above) in the half of the column's
+//     parity (low for even columns, where the diagonal operand needs it), and
+//     in the other half the f16 subnormal zc = -z 2^-24 (-z 2^-20 for columns
+//     r >= 2), so that s' * zc is the offset of the scaled weights;
+//   symmetric: 16 bits of s or s' per column; a lane loads the 32-bit pair of
+//     columns that holds its own, and z = 8 is supplied by the kernel.
+constexpr uint32_t kZcSymmetric = 0xC308u;      // bf16 -136
+constexpr uint32_t kSzBytesSym = 2, kSzBytesAsym = 4;
+
+// f16 zero-point offset of column n16 (z integer in [0, 15])
+__host__ __device__ inline uint32_t f16_zc(uint32_t z, int n16) { return 0x8000u | ((n16 & 2) ? z << 4 : z); }
 
 template <bool SYM>
-__device__ inline uint32_t load_sz_nt(const void *sz, size_t idx) {   // non-temporal, as load_block_nt
-    if constexpr (SYM) {
-        return (uint32_t)__builtin_nontemporal_load((const uint16_t *)sz + idx) | (kZcSymmetric << 16);
-    } else {
-        return __builtin_nontemporal_load((const uint32_t *)sz + idx);
-    }
+__device__ inline uint32_t sz_offset_bytes(int n16) { return SYM ? (uint32_t)(n16 >> 1) * 4u : (uint32_t)n16 * 4u; }
+
+template <bool SYM>
+__device__ inline uint32_t load_sz(const void *sz, size_t block, int n16) {
+    return *(const uint32_t *)((const char *)sz + block * (kTileN * (SYM ? kSzBytesSym : kSzBytesAsym)) +
+                               sz_offset_bytes<SYM>(n16));
+}
+template <bool SYM>
+__device__ inline uint32_t load_sz_nt(const void *sz, size_t block, int n16) {   // non-temporal, as load_block_nt
+    return __builtin_nontemporal_load(
+        (const uint32_t *)((const char *)sz + block * (kTileN * (SYM ? kSzBytesSym : kSzBytesAsym)) +
+                           sz_offset_bytes<SYM>(n16)));
 }
 
 __device__ inline float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2bf, a), __builtin_bit_cast(v2bf, b), c, false);
 }
 
-// c = s * zc of a dequantization word, exactly (one bf16 product, plus 0)
-__device__ inline float sz_offset(uint32_t sz) { return dot2(sz, sz >> 16, 0.0f); }
-
 // --- matrix-core dequantization ------------------------------------------
 
 struct MfmaDeq { v4s bdiag; v4f c4; };
 
-// Byte selectors (v_perm_b32) that place the bf16 s of a dequantization
-// word into element l & 3 of lane l's B operand (two dwords, four bf16) and
-// zero the other three elements.  Constant per lane; built once per kernel.
-struct DiagSel {
-    uint32_t s0, s1;
-    __device__ inline explicit DiagSel(int lane) {
+// Per-lane constants (column l & 15) that turn a loaded dequantization word
+// into B = diag(s) in the 4x4 block layout (lane l supplies B[r][l & 3],
+// non-zero only for r = l & 3: element l & 3 of four 16-bit elements) and the
+// offset C = zc * s.  Built once per kernel.
+template <bool SYM, bool F16>
+struct DeqSel;
+
+template <bool SYM>
+struct DeqSel<SYM, false> {
+    uint32_t s0, s1, half;          // byte selectors (v_perm_b32)
+    __device__ inline explicit DeqSel(int lane) {
         constexpr uint32_t kLo = 0x0C0C0100u, kHi = 0x01000C0Cu, kZero = 0x0C0C0C0Cu;
         const int r = lane & 3;
         s0 = r == 0 ? kLo : r == 1 ? kHi : kZero;
         s1 = r == 2 ? kLo : r == 3 ? kHi : kZero;
+        half = (lane & 1) ? 0x05040302u : 0x05040100u;    // this column's half of the pair, zc above it
+    }
+    __device__ inline uint32_t word(uint32_t raw) const {
+        if constexpr (SYM) return __builtin_amdgcn_perm(kZcSymmetric, raw, half);
+        else return raw;
+    }
+    __device__ inline MfmaDeq setup(uint32_t raw) const {
+        const uint32_t sz = word(raw);
+        const float c = dot2(sz, sz >> 16, 0.0f);         // s * zc, exactly (one bf16 product, plus 0)
+        MfmaDeq d;
+        d.bdiag = __builtin_bit_cast(v4s, v2u{__builtin_amdgcn_perm(sz, sz, s0), __builtin_amdgcn_perm(sz, sz, s1)});
+        d.c4 = v4f{c, c, c, c};
+        return d;
     }
 };
 
-// Per-group constants of lane l for column n = 16 t + (l & 15):
-// B = diag(s) in the 4x4 block layout (this lane supplies B[r][l & 3],
-// non-zero only for r = l & 3) and C = zc * s = -(128 + z) * s in all four rows.
-__device__ inline MfmaDeq mfma_setup(uint32_t sz, const DiagSel &sel) {
-    const float c = sz_offset(sz);
-    MfmaDeq d;
-    d.bdiag = __builtin_bit_cast(v4s, v2u{__builtin_amdgcn_perm(sz, sz, sel.s0), __builtin_amdgcn_perm(sz, sz, sel.s1)});
-    d.c4 = v4f{c, c, c, c};
-    return d;
-}
+template <bool SYM>
+struct DeqSel<SYM, true> {
+    uint32_t m0, m1, own, zc;       // halves of the two dwords of B; this column's half of a pair; z = 8
+    __device__ inline explicit DeqSel(int lane) {
+        const int r = lane & 3;
+        own = (r & 1) ? 0xFFFF0000u : 0x0000FFFFu;
+        m0 = r < 2 ? own : 0u;
+        m1 = r < 2 ? 0u : own;
+        zc = f16_zc(8, r) << ((r & 1) ? 0 : 16);
+    }
+    __device__ inline MfmaDeq setup(uint32_t raw) const {
+        const uint32_t sz = SYM ? ((raw & own) | zc) : raw;
+        float c;                                          // s' * zc, exactly (12 significant bits)
+        asm("v_fma_mix_f32 %0, %1, %1, 0 op_sel:[0,1,0] op_sel_hi:[1,1,0]" : "=v"(c) : "v"(sz));
+        MfmaDeq d;
+        d.bdiag = __builtin_bit_cast(v4s, v2u{raw & m0, raw & m1});
+        d.c4 = v4f{c, c, c, c};
+        return d;
+    }
+};
 
 // Dequantize one packed word into the 8 bf16 A-operand values of
 // v_mfma_f32_16x16x32_bf16 (row n = l & 15): element e holds
-// w[n][32j + 8(l >> 4) + e].
-__device__ inline v8bf mfma_dequant(uint32_t P, const MfmaDeq &d, const ExtractConsts &k) {
-    const Pairs a = extract_pairs(P, k);
-    const v4s A0 = __builtin_bit_cast(v4s, v2u{a.a0, a.a1});
-    const v4s A1 = __builtin_bit_cast(v4s, v2u{a.a2, a.a3});
-    const v4f d0 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(A0, d.bdiag, d.c4, 0, 0, 0);
-    const v4f d1 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(A1, d.bdiag, d.c4, 0, 0, 0);
+// w[n][32j + 8(l >> 4) + e] (times 2^(kF16Exp - 24) for F16).
+template <bool F16>
+__device__ inline v8bf mfma_dequant(uint32_t P, const MfmaDeq &d, const ExtractConsts<F16> &k) {
+    const Pairs a = k.pairs(P);
+    const v2u A0 = {a.a0, a.a1}, A1 = {a.a2, a.a3};
+    v4f d0, d1;
+    if constexpr (F16) {
+        d0 = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(v4h, A0), __builtin_bit_cast(v4h, d.bdiag), d.c4, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(v4h, A1), __builtin_bit_cast(v4h, d.bdiag), d.c4, 0, 0, 0);
+    } else {
+        d0 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(v4s, A0), d.bdiag, d.c4, 0, 0, 0);
+        d1 = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(v4s, A1), d.bdiag, d.c4, 0, 0, 0);
+    }
     const v4u w = {cvt_pk_bf16(d0[0], d0[1]), cvt_pk_bf16(d0[2], d0[3]),
                    cvt_pk_bf16(d1[0], d1[1]), cvt_pk_bf16(d1[2], d1[3])};
     return __builtin_bit_cast(v8bf, w);
@@ -162,24 +245,41 @@ __device__ inline v8bf mfma_dequant(uint32_t P, const MfmaDeq &d, const ExtractC
 
 // --- vector-ALU dequantization -------------------------------------------
 
-// Constants for the four columns n = 16 t + 4 * ((l >> 2) & 3) + r of lane l.
+// Constants for the four columns n = 16 t + 4 * ((l >> 2) & 3) + r of lane l,
+// from words s | zc << 16 in bf16 (the F16 = false form).
 struct ValuDeq { uint32_t sl[4], sh[4]; float c[4]; };
 
 __device__ inline ValuDeq valu_setup(const uint32_t sz[4]) {
     ValuDeq d;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        d.c[r] = sz_offset(sz[r]);   // -(128 + z) * s
+        d.c[r] = dot2(sz[r], sz[r] >> 16, 0.0f);   // -(128 + z) * s
         d.sl[r] = sz[r] & 0xFFFFu;   // bf16 pair (s, 0)
         d.sh[r] = sz[r] << 16;       // bf16 pair (0, s)
     }
     return d;
 }
 
+// The bf16 word s | zc << 16 of column r of a 4-column block from what a
+// handle stores for it (v = the 32-bit word, or for symmetric handles the 16
+// bits in the half of the column's parity).  For f16 = true the scale comes
+// out as s 2^(kF16Exp - 24): the weights have the scaling of the matrix-core
+// route.
+template <bool SYM>
+__device__ inline uint32_t valu_word(uint32_t v, int r, bool f16) {
+    const uint32_t own = (r & 1) ? v >> 16 : v & 0xFFFFu, other = (r & 1) ? v & 0xFFFFu : v >> 16;
+    if (f16) {
+        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)own) * (r >= 2 ? 0x1p-20f : 0x1p-24f);
+        const uint32_t z = SYM ? 8u : (other & 0x7FFFu) >> (r >= 2 ? 4 : 0);
+        return (__float_as_uint(s) >> 16) | ((0xC300u | z) << 16);
+    }
+    return SYM ? (own | (kZcSymmetric << 16)) : v;
+}
+
 // Dequantize one packed word: pr[r] = bf16 pair (w[n_r][k0], w[n_r][k0 + 4]) with
 // k0 = 32j + 8(l >> 4) + (l & 3).
-__device__ inline void valu_dequant(uint32_t P, const ValuDeq &d, const ExtractConsts &k, uint32_t pr[4]) {
-    const Pairs a = extract_pairs(P, k);
+__device__ inline void valu_dequant(uint32_t P, const ValuDeq &d, const ExtractConsts<false> &k, uint32_t pr[4]) {
+    const Pairs a = k.pairs(P);
     const float w00 = dot2(a.a0, d.sl[0], d.c[0]), w01 = dot2(a.a0, d.sh[1], d.c[1]);
     const float w02 = dot2(a.a1, d.sl[2], d.c[2]), w03 = dot2(a.a1, d.sh[3], d.c[3]);
     const float w10 = dot2(a.a2, d.sl[0], d.c[0]), w11 = dot2(a.a2, d.sh[1], d.c[1]);

@@ -30,11 +30,12 @@
 // v_dot2_f32_bf16 on the same extracted pairs.  Both routes are bit-identical
 // to the definition; the unpack/dequantize test hooks check that.
 
-#include "device_common.h"
+#include "decode_common.h"
 
 #include <algorithm>
 #include <cstdio>
 #include <mutex>
+#include <type_traits>
 
 namespace qlin {
 
@@ -63,7 +64,7 @@ __global__ void k_repack_codes(const uint32_t *__restrict__ canon, uint32_t *__r
 }
 
 __global__ void k_repack_sz(const uint16_t *__restrict__ scales, const uint16_t *__restrict__ zeros,
-                            void *__restrict__ out, int K, int N, int symmetric) {
+                            void *__restrict__ out, int K, int N, int symmetric, int f16) {
     const int Kb = K / kGroup;
     const size_t total = (size_t)N * Kb;
     for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
@@ -73,11 +74,18 @@ __global__ void k_repack_sz(const uint16_t *__restrict__ scales, const uint16_t 
         const int t = (int)(tb / Kb), kb = (int)(tb % Kb);
         const size_t n = (size_t)t * kTileN + n16;
         const uint16_t s = scales[n * Kb + kb];
-        if (symmetric) {
+        // z is an integer in [0, 15]
+        const uint32_t z = symmetric ? 8u : (uint32_t)__uint_as_float((uint32_t)zeros[n * Kb + kb] << 16);
+        if (f16) {
+            const float sv = __uint_as_float((uint32_t)s << 16) * (n16 & 2 ? __builtin_ldexpf(1.0f, kF16Exp - 4)
+                                                                          : __builtin_ldexpf(1.0f, kF16Exp));
+            const uint32_t h = __builtin_bit_cast(uint16_t, (_Float16)sv), zc = f16_zc(z, n16);   // exact
+            if (symmetric) ((uint16_t *)out)[idx] = (uint16_t)h;
+            else ((uint32_t *)out)[idx] = (n16 & 1) ? (h << 16) | zc : h | (zc << 16);
+        } else if (symmetric) {
             ((uint16_t *)out)[idx] = s;
         } else {
-            // zc = -(128 + z): bf16 sign 1, exponent of 128, mantissa z (z integer in [0, 15])
-            const uint32_t z = (uint32_t)__uint_as_float((uint32_t)zeros[n * Kb + kb] << 16);
+            // zc = -(128 + z): bf16 sign 1, exponent of 128, mantissa z
             ((uint32_t *)out)[idx] = (uint32_t)s | ((0xC300u | z) << 16);
         }
     }
@@ -103,28 +111,31 @@ __global__ void k_unpack(const uint4 *__restrict__ codes, uint8_t *__restrict__ 
     }
 }
 
-template <bool SYM>
+// Both dequantizing hooks undo the F16 route's power-of-two scaling (exactly)
+// before they store.
+template <bool SYM, bool F16>
 __global__ void k_dequant_mfma(const uint4 *__restrict__ codes, const void *__restrict__ sz,
                                uint16_t *__restrict__ w, int K, int N) {
     const int Kb = K / kGroup;
     const size_t nblocks = (size_t)(N / kTileN) * Kb;
     const int l = threadIdx.x & 63;
-    const DiagSel dsel(l);
-    const ExtractConsts kx;
+    const DeqSel<SYM, F16> dsel(l);
+    const ExtractConsts<F16> kx;
     for (size_t b = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nblocks;
          b += (size_t)gridDim.x * (blockDim.x >> 6)) {
         const uint4 c = codes[b * 64 + l];
-        const MfmaDeq d = mfma_setup(load_sz<SYM>(sz, b * kTileN + (l & 15)), dsel);
+        const MfmaDeq d = dsel.setup(load_sz<SYM>(sz, b, l & 15));
         const uint32_t P[4] = {c.x, c.y, c.z, c.w};
         const int t = (int)(b / Kb), kb = (int)(b % Kb);
         const size_t n = (size_t)t * kTileN + (l & 15);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const v4u v = __builtin_bit_cast(v4u, mfma_dequant(P[j], d, kx));
+            const v4u v = __builtin_bit_cast(v4u, mfma_dequant<F16>(P[j], d, kx));
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = kb * kGroup + 32 * j + 8 * (l >> 4) + e;
-                w[n * K + k] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+                const uint32_t bits = (v[e >> 1] >> (16 * (e & 1))) << 16;
+                w[n * K + k] = (uint16_t)(__float_as_uint(__uint_as_float(bits) * (F16 ? kF16Unscale : 1.0f)) >> 16);
             }
         }
     }
@@ -132,17 +143,18 @@ __global__ void k_dequant_mfma(const uint4 *__restrict__ codes, const void *__re
 
 template <bool SYM>
 __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__restrict__ sz,
-                               uint16_t *__restrict__ w, int K, int N) {
+                               uint16_t *__restrict__ w, int K, int N, int f16) {
     const int Kb = K / kGroup;
     const size_t nblocks = (size_t)(N / kTileN) * Kb;
     const int l = threadIdx.x & 63;
     const int b2 = (l >> 2) & 3;
-    const ExtractConsts kx;
+    const ExtractConsts<false> kx;
+    const float unscale = f16 ? kF16Unscale : 1.0f;
     for (size_t b = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nblocks;
          b += (size_t)gridDim.x * (blockDim.x >> 6)) {
         const uint4 c = codes[b * 64 + l];
         uint32_t s4[4];
-        for (int r = 0; r < 4; ++r) s4[r] = load_sz<SYM>(sz, b * kTileN + 4 * b2 + r);
+        for (int r = 0; r < 4; ++r) s4[r] = valu_word<SYM>(load_sz<SYM>(sz, b, 4 * b2 + r), r, f16);
         const ValuDeq d = valu_setup(s4);
         const uint32_t P[4] = {c.x, c.y, c.z, c.w};
         const int t = (int)(b / Kb), kb = (int)(b % Kb);
@@ -152,8 +164,8 @@ __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__re
             for (int r = 0; r < 4; ++r) {
                 const size_t n = (size_t)t * kTileN + 4 * b2 + r;
                 const int k0 = kb * kGroup + 32 * j + 8 * (l >> 4) + (l & 3);
-                w[n * K + k0] = (uint16_t)(pr[r] & 0xFFFFu);
-                w[n * K + k0 + 4] = (uint16_t)(pr[r] >> 16);
+                w[n * K + k0] = (uint16_t)(__float_as_uint(bf16_lo_to_f32(pr[r]) * unscale) >> 16);
+                w[n * K + k0 + 4] = (uint16_t)(__float_as_uint(bf16_hi_to_f32(pr[r]) * unscale) >> 16);
             }
         }
     }
@@ -161,191 +173,12 @@ __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__re
 
 // ------------------------------------------------------------------ forward
 
-// Column range, member and K chunk of workgroup `bid`: chunk c, range jn
-// (over all members), the member's tiles [t0, t0 + Tn) and groups
-// [g0, g0 + Kc), and the member's weights and output.
-struct WgWork {
-    int c, jn, t0, Tn, g0, Kc;
-    const uint4 *codes;
-    const void *sz;
-    uint16_t *y;
-    int N;
-};
-// Everything here is wave-uniform scalar work at the start of the kernel:
-// the arguments arrive in one batch of scalar loads (the range starts are one
-// contiguous array, every index static, and the chunk needs no division),
-// then the member's fields in one more.
-__device__ inline WgWork wg_work(const FwdArgs &a, int bid) {
-    WgWork w;
-    // bid / Gn as a multiply-high by ceil(2^32 / Gn): exact because bid * Gn
-    // stays below 2^32 (bid < 64 * 4096 workgroups, Gn <= 4096); for Gn = 1
-    // the reciprocal is 0 and the chunk is bid itself
-    w.c = (int)(__umulhi((uint32_t)bid, a.inv_gn) + (a.Gn == 1 ? (uint32_t)bid : 0u));
-    w.jn = bid - w.c * a.Gn;
-    int m = 0, g0 = 0;                        // the member owning range jn, its first range
-#pragma unroll
-    for (int i = 1; i < kMaxMembers; ++i)
-        if (w.jn >= a.gn0[i]) {
-            m = i;
-            g0 = a.gn0[i];
-        }
-    // one scalar load of the member's fields at a computed offset (reading a
-    // member at a fixed index as well would make the compiler copy the
-    // whole argument block to scratch memory)
-    const FwdMember &f = a.mem[m];
-    w.codes = f.codes;
-    w.sz = f.sz;
-    w.y = f.y;
-    w.N = f.N;
-    const int j = w.jn - g0;
-    w.t0 = j * f.Nq + min(j, f.Nr);
-    w.Tn = f.Nq + (j < f.Nr ? 1 : 0);
-    w.g0 = w.c * a.Kq + min(w.c, a.Kr);
-    w.Kc = a.Kq + (w.c < a.Kr ? 1 : 0);
-    return w;
-}
-
 // Range [u0, u1) of the U = Tn * Kc blocks (tile-major) that wave i of a
 // workgroup handles: U / kWaves blocks each, one more for the first U % kWaves.
 __device__ inline void wave_range(int U, int i, int &u0, int &u1) {
     const int q = U / kWaves, r = U % kWaves;    // kWaves is a power of two
     u0 = i * q + min(i, r);
     u1 = u0 + q + (i < r ? 1 : 0);
-}
-
-// Split-K partial sums travel between workgroups that may sit on different
-// XCDs, whose L2 caches are not coherent with each other for ordinary
-// accesses.  They are written and read with agent-scope (sc1) buffer
-// accesses, which the hardware performs at the device coherence point; an
-// agent-scope release/acquire fence instead would write back and invalidate
-// the whole L2 of the XCD on every arrival.  Workgroup (c, jn) owns a
-// contiguous region of TnMax * M * 16 fp32 at ((c * Gn + jn) * TnMax * M * 16),
-// item it = (tile * M + m) * 2 + half at float offset 8 * it, so the 16-byte
-// accesses of a wave are contiguous.
-
-__device__ inline __amdgpu_buffer_rsrc_t ws_rsrc(const FwdArgs &a) {
-    return __builtin_amdgcn_make_buffer_rsrc(a.ws, 0, (int)a.ws_bytes, kRsrcFlags);
-}
-__device__ inline uint32_t ws_region(const FwdArgs &a, int c, int jn) {      // byte offset
-    return (uint32_t)((c * a.Gn + jn) * a.TnMax * a.M) * 64u;
-}
-// The four sums of quarter row `it` of the workgroup's output (row m,
-// columns n .. n + 3): bf16 straight to y when the whole K range is covered,
-// else fp32 partials to the workspace, quarter it at float offset 4 it of the
-// region (half row h = (tile * M + m) * 2 + half is quarters 2h and 2h + 1).
-__device__ inline void store_quarter(const FwdArgs &a, const WgWork &w, int it, int m, int n, const float s[4],
-                                     bool direct) {
-    if (direct) {
-        *(uint2 *)(w.y + (size_t)m * w.N + n) = make_uint2(cvt_pk_bf16(s[0], s[1]), cvt_pk_bf16(s[2], s[3]));
-    } else {
-        const uint32_t off = ws_region(a, w.c, w.jn) + (uint32_t)it * 16u;
-        __builtin_amdgcn_raw_buffer_store_b128(
-            v4u{__float_as_uint(s[0]), __float_as_uint(s[1]), __float_as_uint(s[2]), __float_as_uint(s[3])},
-            ws_rsrc(a), off, 0, kSc1);
-    }
-}
-
-// The last of the S workgroups of a column range adds the S fp32 partials in
-// chunk order (fixed order) and writes y.
-__device__ inline void reduce_chunks(const FwdArgs &a, const WgWork &w) {
-    const int tid = threadIdx.x;
-    const int items = w.Tn * a.M * 2;
-    // Every wave waits until its partial-sum stores have completed at the
-    // device coherence point before the barrier; one relaxed atomic per
-    // workgroup then counts the arrival.  The last arrival reads the other
-    // workgroups' partials with agent-scope loads, which do not hit stale
-    // cached copies.
-    __shared__ int s_last;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) {
-        const uint32_t old = __hip_atomic_fetch_add(&a.counters[w.jn], 1u, __ATOMIC_RELAXED,
-                                                    __HIP_MEMORY_SCOPE_AGENT);
-        s_last = (old == (uint32_t)(a.S - 1));
-    }
-    __syncthreads();
-    if (!s_last) return;
-    const __amdgpu_buffer_rsrc_t r = ws_rsrc(a);
-    const uint32_t inv_pt = 0xFFFFFFFFu / (uint32_t)(a.M * 2) + 1u;   // as in write_out()
-    for (int it = tid; it < items; it += kThreads) {
-        const int tl = (int)__umulhi((uint32_t)it, inv_pt);
-        const int rem = it - tl * a.M * 2;
-        const int m = rem >> 1, hh = rem & 1;
-        const size_t n = (size_t)(w.t0 + tl) * kTileN + 8 * hh;
-        // partials of kBatch chunks are loaded together (one memory round
-        // trip per batch, not per chunk), then added in chunk order
-        constexpr int kBatch = 8;
-        float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int c0 = 0; c0 < a.S; c0 += kBatch) {
-            v4u v[kBatch][2];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) {
-                const int cc = min(c0 + u, a.S - 1);      // unconditional load; extra ones are not added
-                const uint32_t off = ws_region(a, cc, w.jn) + (uint32_t)it * 32u;
-                v[u][0] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kSc1);
-                v[u][1] = __builtin_amdgcn_raw_buffer_load_b128(r, off + 16, 0, kSc1);
-            }
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u)
-                if (c0 + u < a.S)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) s[i] += __uint_as_float(v[u][i >> 2][i & 3]);
-        }
-        uint4 o;
-        o.x = cvt_pk_bf16(s[0], s[1]);
-        o.y = cvt_pk_bf16(s[2], s[3]);
-        o.z = cvt_pk_bf16(s[4], s[5]);
-        o.w = cvt_pk_bf16(s[6], s[7]);
-        *(uint4 *)(w.y + (size_t)m * w.N + n) = o;
-    }
-    if (tid == 0) __hip_atomic_store(&a.counters[w.jn], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Writes the workgroup's results.  Each wave left one partial sum per column
-// tile it touched in LDS slot (wave, tile), and zeros (from the kernel's start)
-// in the slots of the tiles it did not touch; the tile's sum adds the slots of
-// all waves in wave order.  With the whole K range covered (S == 1) the sum goes to y as
-// bf16; otherwise it goes to the fp32 workspace, and the last of the S
-// workgroups of this column range adds the S partials in chunk order and
-// writes y.  Every sum runs in a fixed order, so results do not depend on
-// timing: repeated calls give identical bits.
-//
-// The loop strides by the compile-time workgroup size: blockDim.x would be a
-// scalar load of the dispatch's hidden arguments here, after the main loop,
-// and that load misses the scalar cache and costs a memory round trip on the
-// workgroup's critical path.
-//
-// An item's slot reads do not depend on each other: all kWaves of them are
-// issued before the first add.  Adding the zero slots leaves a sum's bits
-// unchanged (the sum starts at +0), so the result equals the sum of the
-// touched slots alone, without a per-slot test.
-__device__ inline void write_out(const FwdArgs &a, const WgWork &w, const float *slots, int rows) {
-    const int tid = threadIdx.x;
-    const int per_tile = a.M * 4;                  // items (quarter rows of 4 columns) per tile
-    const int items = w.Tn * per_tile;
-    const bool direct = (a.S == 1);
-    // tile of an item: a multiply-high by ceil(2^32 / per_tile), exact since
-    // items and per_tile stay below 2^16
-    const uint32_t inv_pt = 0xFFFFFFFFu / (uint32_t)per_tile + 1u;
-    for (int it = tid; it < items; it += kThreads) {
-        const int tl = (int)__umulhi((uint32_t)it, inv_pt);
-        const int rem = it - tl * per_tile;
-        const int m = rem >> 2, qq = rem & 3;
-        float4 v[kWaves];
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i)
-            v[i] = *(const float4 *)(slots + ((size_t)(i * w.Tn + tl) * rows + m) * 16 + 4 * qq);
-        float s[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
-            s[0] += v[i].x;
-            s[1] += v[i].y;
-            s[2] += v[i].z;
-            s[3] += v[i].w;
-        }
-        store_quarter(a, w, it, m, (w.t0 + tl) * kTileN + 4 * qq, s, direct);
-    }
-    if (!direct) reduce_chunks(a, w);
 }
 
 // ---- SKINNY: matrix-core dequantization + v_mfma_f32_16x16x32_bf16 --------
@@ -357,7 +190,7 @@ __device__ inline void write_out(const FwdArgs &a, const WgWork &w, const float 
 // flight; its waves then split the Tn * Kc blocks evenly (tile-major order),
 // each keeping kDepth 1 KiB blocks in flight.  A wave leaves one partial sum
 // per tile it touches in its LDS slot for that tile (slots start at zero);
-// write_out() adds the waves' slots in a fixed order.
+// write_sums() adds the waves' slots in a fixed order.
 //
 // x in LDS: 16-byte fragments, fragment (row, q8) = x[row][k0 .. k0 + 8)
 // with k0 = 128 g0 + 8 q8 (q8 = 16 kbl + c, c = 4j + g < 16), row-major at
@@ -367,16 +200,14 @@ __device__ inline void write_out(const FwdArgs &a, const WgWork &w, const float 
 // shifts consecutive rows by 4 banks, so the operand reads (16 lanes = 16
 // rows of one q8) hit distinct banks; and a lane's four reads of a block are
 // one address plus immediate offsets (4 j slots).  XR = staged rows (the
-// next power of two >= M for one m-tile, else 16 MT).  Lane l of m-tile mt
-// reads row min(16 mt + (l & 15), M - 1); pad slots and rows >= M hold
-// copies and are never read.
-template <int MT, int XR, bool SYM>
+// next power of two >= M).  Lane l reads row min(l & 15, M - 1); pad slots and
+// rows >= M hold copies and are never read.
+template <int XR, bool SYM>
 __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MR = 16 * MT;
+    constexpr int MR = 16;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps the walk on the scalar unit
-    const ExtractConsts kx;
     const WgWork w = wg_work(a, blockIdx.x);
     uint4 *xs = (uint4 *)smem;
     const int n8 = w.Kc * 16;                         // 16-byte chunks per row of the x chunk
@@ -388,7 +219,6 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
     int u0, u1;
     wave_range(U, wave, u0, u1);
     const int lm = lane & 15, lg = lane >> 4;
-    const DiagSel dsel(lane);
 
     // 1) the x chunk, straight into LDS: load i fills slots [64 i, 64 i + 64)
     //    (the last one may run past the chunk into spare LDS).  The row of a
@@ -428,77 +258,68 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
     const size_t base = (size_t)w.t0 * a.Kb + w.g0;
     const uint32_t skip = (uint32_t)(a.Kb - w.Kc);
     const uint32_t ulast = (uint32_t)(u0 < u1 ? u1 - 1 : min(u0, U - 1));
-    constexpr int kSzBytes = SYM ? 2 : 4;
+    constexpr int kSzBytes = SYM ? kSzBytesSym : kSzBytesAsym;
+    const int sz_lane = (int)sz_offset_bytes<SYM>(lm);
     const int span = w.Tn * a.Kb;                      // blocks from base to past the workgroup's last
     const __amdgpu_buffer_rsrc_t rcodes =
         __builtin_amdgcn_make_buffer_rsrc((void *)(w.codes + base * 64), 0, span * 1024, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rsz = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const char *)w.sz + base * kTileN * kSzBytes), 0, span * kTileN * kSzBytes, kRsrcFlags);
-    uint4 cb[kDepth];
-    uint32_t sb[kDepth];
-    auto fetch = [&](int d, uint32_t u) {
-        u = min(u, ulast);
-        const uint32_t rb = u + tile_of(u) * skip;                // block relative to base
-        cb[d] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rcodes, lane * 16, rb * 1024, kWeightPolicy));
-        if constexpr (SYM) {
-            sb[d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rsz, lm * 2, rb * (kTileN * 2), kWeightPolicy) |
-                    (kZcSymmetric << 16);
-        } else {
-            sb[d] = __builtin_amdgcn_raw_buffer_load_b32(rsz, lm * 4, rb * (kTileN * 4), kWeightPolicy);
-        }
-    };
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) fetch(d, (uint32_t)(u0 + d));
-    // the partial-sum slots start at zero (a wave writes only the slots of
-    // the tiles it touches); the barrier below orders this before any write
-    {
-        const int nq = kWaves * w.Tn * MR * 4;     // 16-byte words
-        for (int i = tid; i < nq; i += kThreads) ((float4 *)slots)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
-    // 3) every wave's x loads have landed in LDS (only the weight prefetch,
-    //    2 kDepth loads, may still be in flight)
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kDepth) : "memory");
-    lds_barrier();
-
     // per-lane part of the operand read slot: q8 = 16 kbl + 4 j + lg, so the
-    // slot is 16 kbl + 4 j + xoff[mt]
-    int xoff[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) xoff[mt] = min(16 * mt + lm, a.M - 1) * (n8 + 1) + lg;
+    // slot is 16 kbl + 4 j + xoff
+    const int xoff = min(lm, a.M - 1) * (n8 + 1) + lg;
 
-    if (u0 < u1) {
-        v4f acc[MT];
+    // the whole walk exists once per dequantization route (uniform in the
+    // workgroup: its tiles belong to one member), its first loads included,
+    // so that none in flight is copied between the routes' registers
+    auto walk = [&](auto route) {
+        constexpr bool F16 = decltype(route)::value;
+        const ExtractConsts<F16> kx;
+        const DeqSel<SYM, F16> dsel(lane);
+        uint4 cb[kDepth];
+        uint32_t sb[kDepth];
+        auto fetch = [&](int d, uint32_t u) {
+            u = min(u, ulast);
+            const uint32_t rb = u + tile_of(u) * skip;                // block relative to base
+            cb[d] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rcodes, lane * 16, rb * 1024, kWeightPolicy));
+            sb[d] = __builtin_amdgcn_raw_buffer_load_b32(rsz, sz_lane, rb * (kTileN * kSzBytes), kWeightPolicy);
+        };
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = v4f{0, 0, 0, 0};
+        for (int d = 0; d < kDepth; ++d) {
+            fetch(d, (uint32_t)(u0 + d));
+            asm volatile("" ::: "memory");     // block by block: the first block's scales are not behind the last block's codes
+        }
+        // the partial-sum slots start at zero (a wave writes only the slots of
+        // the tiles it touches); the barrier below orders this before any write
+        {
+            const int nq = kWaves * w.Tn * MR * 4;     // 16-byte words
+            for (int i = tid; i < nq; i += kThreads) ((float4 *)slots)[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        // 3) every wave's x loads have landed in LDS (only the weight prefetch,
+        //    2 kDepth loads, may still be in flight)
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * kDepth) : "memory");
+        lds_barrier();
+        if (u0 >= u1) return;
+        v4f acc = v4f{0, 0, 0, 0};
 
         auto consume = [&](uint32_t u, const uint4 &cq, uint32_t szw) {
             const uint32_t tl = tile_of(u);
             const uint32_t kbl = u - tl * (uint32_t)w.Kc;
-            v8bf xf[MT][4];
+            v8bf xf[4];
+            const uint4 *xb = xs + kbl * 16 + xoff;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const uint4 *xb = xs + kbl * 16 + xoff[mt];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) xf[mt][j] = __builtin_bit_cast(v8bf, xb[4 * j]);
-            }
-            const MfmaDeq d = mfma_setup(szw, dsel);
+            for (int j = 0; j < 4; ++j) xf[j] = __builtin_bit_cast(v8bf, xb[4 * j]);
+            const MfmaDeq d = dsel.setup(szw);
             const uint32_t P[4] = {cq.x, cq.y, cq.z, cq.w};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const v8bf wa = mfma_dequant(P[j], d, kx);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[mt][j], acc[mt], 0, 0, 0);
-            }
+            for (int j = 0; j < 4; ++j)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mfma_dequant<F16>(P[j], d, kx), xf[j], acc, 0, 0, 0);
             // the tile's run in this wave ends here (rare: kept off the
             // straight-line path)
             if (__builtin_expect(kbl == (uint32_t)w.Kc - 1u || u == (uint32_t)u1 - 1u, 0)) {
                 // D of the 16x16 op: lane l holds rows n = 4(l >> 4) + v of column m = l & 15
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    *(v4f *)(slots + ((size_t)(wave * w.Tn + tl) * MR + 16 * mt + lm) * 16 + 4 * lg) = acc[mt];
-                    acc[mt] = v4f{0, 0, 0, 0};
-                }
+                *(v4f *)(slots + ((size_t)(wave * w.Tn + tl) * MR + lm) * 16 + 4 * lg) = acc;
+                acc = v4f{0, 0, 0, 0};
             }
         };
 
@@ -513,9 +334,11 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
 #pragma unroll
         for (int d = 0; d < kDepth; ++d)
             if (u + d < u1) consume((uint32_t)(u + d), cb[d], sb[d]);
-    }
+    };
+    if (w.f16) walk(std::true_type{});
+    else walk(std::false_type{});
     lds_barrier();
-    write_out(a, w, slots, MR);
+    write_sums<kWaves>(a, w, slots, w.Tn, MR);
 }
 
 // ---- register-resident kernels (M <= 16) -------------------------------
@@ -528,42 +351,11 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
 // of its tiles' blocks (contiguous KiB in the device layout) plus that
 // group's x, one group ahead of the compute (group_ring with two buffers).
 // Each wave keeps one accumulator per tile; at the end it writes them to its
-// LDS slots and write_out_waves() adds the waves' slots in wave order.
+// LDS slots and write_sums() adds the waves' slots in wave order.
 //
 // Out-of-range tiles of a wave's first and last group still load (a valid
 // block of the group) so that the loads stay unconditional and the compiler
 // can count them; they are not computed.
-
-// Sum over the waves' slots (fixed order) and write y, or fp32 partials plus
-// the last-arrival reduction when the K range is cut (S > 1).  Slot (wave, tl)
-// holds rows x 16 fp32 (row-major, 16 columns).
-template <int TN>
-__device__ inline void write_out_waves(const FwdArgs &a, const WgWork &w, const float *slots, int rows) {
-    const int tid = threadIdx.x;
-    const int per_tile = a.M * 4;                  // items (quarter rows of 4 columns) per tile
-    const int items = w.Tn * per_tile;
-    const bool direct = (a.S == 1);
-    const uint32_t inv_pt = 0xFFFFFFFFu / (uint32_t)per_tile + 1u;   // as in write_out()
-    for (int it = tid; it < items; it += kThreads) {
-        const int tl = (int)__umulhi((uint32_t)it, inv_pt);
-        const int rem = it - tl * per_tile;
-        const int m = rem >> 2, qq = rem & 3;
-        float4 v[kWaves];
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i)
-            v[i] = *(const float4 *)(slots + (((size_t)i * TN + tl) * rows + m) * 16 + 4 * qq);
-        float s[4] = {0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
-            s[0] += v[i].x;
-            s[1] += v[i].y;
-            s[2] += v[i].z;
-            s[3] += v[i].w;
-        }
-        store_quarter(a, w, it, m, (w.t0 + tl) * kTileN + 4 * qq, s, direct);
-    }
-    if (!direct) reduce_chunks(a, w);
-}
 
 // Group buffers in flight per wave.  Deeper rings were measured slower for
 // narrow column ranges: every group also reloads its x fragments (4 KiB per
@@ -631,19 +423,20 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
     float *slots = (float *)smem;                  // [kWaves][TN][16][16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ExtractConsts kx;
     const WgWork w = wg_work(a, blockIdx.x);
     const int Tn = w.Tn;
     int u0, u1;
     wave_range(Tn * w.Kc, wave, u0, u1);
     const int lm = lane & 15, lg = lane >> 4;
-    const DiagSel dsel(lane);
 
     v4f acc[TN];
 #pragma unroll
     for (int t = 0; t < TN; ++t) acc[t] = v4f{0, 0, 0, 0};
 
-    if (u0 < u1) {
+    auto walk = [&](auto route) {            // once per dequantization route, as in k_skinny
+        constexpr bool F16 = decltype(route)::value;
+        const ExtractConsts<F16> kx;
+        const DeqSel<SYM, F16> dsel(lane);
         WaveGroups wg;
         wg.init(u0, u1, Tn);
         auto load_group = [&](MfmaGroup<TN> &B, int kbl) {
@@ -653,7 +446,7 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
             for (int t = 0; t < TN; ++t) {
                 const size_t b = base + (size_t)min(max(t, ta), tb - 1) * a.Kb;
                 B.c[t] = load_block_nt(w.codes, b * 64 + lane);
-                B.s[t] = load_sz_nt<SYM>(w.sz, b * kTileN + lm);
+                B.s[t] = load_sz_nt<SYM>(w.sz, b, lm);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) B.x[j] = load_xfrag(a, w.g0 + kbl, j, lane);
@@ -663,24 +456,28 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
                 if (t >= ta && t < tb) {
-                    const MfmaDeq d = mfma_setup(B.s[t], dsel);
+                    const MfmaDeq d = dsel.setup(B.s[t]);
                     const uint32_t P[4] = {B.c[t].x, B.c[t].y, B.c[t].z, B.c[t].w};
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mfma_dequant(P[j], d, kx), B.x[j], acc[t], 0,
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mfma_dequant<F16>(P[j], d, kx), B.x[j], acc[t], 0,
                                                                          0, 0);
                 }
             }
         };
         MfmaGroup<TN> ring[ring_groups<TN>()];
         group_ring(wg.kg0, wg.kg1, ring, load_group, compute_group);
+    };
+    if (u0 < u1) {
+        if (w.f16) walk(std::true_type{});
+        else walk(std::false_type{});
     }
     // D of the 16x16 op: lane l holds rows n = 4(l >> 4) + v of column m = l & 15
 #pragma unroll
     for (int t = 0; t < TN; ++t)
         if (t < Tn) *(v4f *)(slots + (((size_t)wave * TN + t) * 16 + lm) * 16 + 4 * lg) = acc[t];
     lds_barrier();
-    write_out_waves<TN>(a, w, slots, 16);
+    write_sums<kWaves>(a, w, slots, TN, 16);
 }
 
 // ---- GEMV: vector-ALU dequantization + v_dot2_f32_bf16 (M <= 4) ---------
@@ -701,7 +498,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
     float *slots = (float *)smem;                  // [kWaves][TN][MV][16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ExtractConsts kx;
+    const ExtractConsts<false> kx;
     const WgWork w = wg_work(a, blockIdx.x);
     const int Tn = w.Tn;
     int u0, u1;
@@ -729,8 +526,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
                 B.c[t] = load_block_nt(w.codes, b * 64 + lane);
                 if constexpr (SYM) {
                     const uint2 h = __builtin_bit_cast(uint2, __builtin_nontemporal_load((const v2u *)((const uint16_t *)w.sz + b * kTileN + 4 * b2)));
-                    B.s[t] = make_uint4((h.x & 0xFFFFu) | (kZcSymmetric << 16), (h.x >> 16) | (kZcSymmetric << 16),
-                                        (h.y & 0xFFFFu) | (kZcSymmetric << 16), (h.y >> 16) | (kZcSymmetric << 16));
+                    B.s[t] = make_uint4(h.x, h.x, h.y, h.y);       // valu_word picks the column's half
                 } else {
                     B.s[t] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const v4u *)((const uint32_t *)w.sz + b * kTileN + 4 * b2)));
                 }
@@ -750,7 +546,8 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
                 if (t >= ta && t < tb) {
-                    const uint32_t s4[4] = {B.s[t].x, B.s[t].y, B.s[t].z, B.s[t].w};
+                    const uint32_t s4[4] = {valu_word<SYM>(B.s[t].x, 0, w.f16), valu_word<SYM>(B.s[t].y, 1, w.f16),
+                                            valu_word<SYM>(B.s[t].z, 2, w.f16), valu_word<SYM>(B.s[t].w, 3, w.f16)};
                     const ValuDeq d = valu_setup(s4);
                     const uint32_t P[4] = {B.c[t].x, B.c[t].y, B.c[t].z, B.c[t].w};
 #pragma unroll
@@ -791,7 +588,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
         }
     }
     lds_barrier();
-    write_out_waves<TN>(a, w, slots, MV);
+    write_sums<kWaves>(a, w, slots, TN, MV);
 }
 
 // ------------------------------------------------------------------ quantize + pack
@@ -966,7 +763,7 @@ static inline int grid_for(size_t items, int per_block) {
 }
 
 hipError_t launch_repack(const uint32_t *canon, const uint16_t *scales, const uint16_t *zeros,
-                         uint4 *codes, void *sz, int K, int N, bool symmetric, hipStream_t st) {
+                         uint4 *codes, void *sz, int K, int N, bool symmetric, bool f16, hipStream_t st) {
     const size_t words = (size_t)N * K / 8;
     hipLaunchKernelGGL(k_repack_codes, dim3(grid_for(words, 256)), dim3(256), 0, st,
                        canon, (uint32_t *)codes, K, N);
@@ -974,7 +771,7 @@ hipError_t launch_repack(const uint32_t *canon, const uint16_t *scales, const ui
     if (e != hipSuccess) return e;
     const size_t ent = (size_t)N * (K / kGroup);
     hipLaunchKernelGGL(k_repack_sz, dim3(grid_for(ent, 256)), dim3(256), 0, st,
-                       scales, zeros, sz, K, N, symmetric ? 1 : 0);
+                       scales, zeros, sz, K, N, symmetric ? 1 : 0, f16 ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -984,21 +781,20 @@ hipError_t launch_unpack(const uint4 *codes, uint8_t *q, int K, int N, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool symmetric,
+hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool symmetric, bool f16,
                           uint16_t *w, int K, int N, hipStream_t st) {
     const size_t nblocks = (size_t)(N / kTileN) * (K / kGroup);
     const dim3 g(grid_for(nblocks, 4)), b(256);
     if (routine == 0) {
-        if (symmetric) hipLaunchKernelGGL(k_dequant_mfma<true>, g, b, 0, st, codes, sz, w, K, N);
-        else hipLaunchKernelGGL(k_dequant_mfma<false>, g, b, 0, st, codes, sz, w, K, N);
+        auto kern = symmetric ? (f16 ? k_dequant_mfma<true, true> : k_dequant_mfma<true, false>)
+                              : (f16 ? k_dequant_mfma<false, true> : k_dequant_mfma<false, false>);
+        hipLaunchKernelGGL(kern, g, b, 0, st, codes, sz, w, K, N);
     } else {
-        if (symmetric) hipLaunchKernelGGL(k_dequant_valu<true>, g, b, 0, st, codes, sz, w, K, N);
-        else hipLaunchKernelGGL(k_dequant_valu<false>, g, b, 0, st, codes, sz, w, K, N);
+        auto kern = symmetric ? k_dequant_valu<true> : k_dequant_valu<false>;
+        hipLaunchKernelGGL(kern, g, b, 0, st, codes, sz, w, K, N, f16 ? 1 : 0);
     }
     return hipGetLastError();
 }
-
-typedef void (*FwdKernel)(FwdArgs);
 
 template <int TN, bool SYM>
 static FwdKernel pick_regs(int kern, int mrows) {
@@ -1018,14 +814,11 @@ template <bool SYM>
 static FwdKernel pick(int kern, int mrows, int tn) {
     if (kern == kKernStaged) {        // tn = staged rows XR
         switch (tn) {
-            case 1: return k_skinny<1, 1, SYM>;
-            case 2: return k_skinny<1, 2, SYM>;
-            case 4: return k_skinny<1, 4, SYM>;
-            case 8: return k_skinny<1, 8, SYM>;
-            case 16: return k_skinny<1, 16, SYM>;
-            case 32: return k_skinny<2, 32, SYM>;
-            case 48: return k_skinny<3, 48, SYM>;
-            case 64: return k_skinny<4, 64, SYM>;
+            case 1: return k_skinny<1, SYM>;
+            case 2: return k_skinny<2, SYM>;
+            case 4: return k_skinny<4, SYM>;
+            case 8: return k_skinny<8, SYM>;
+            case 16: return k_skinny<16, SYM>;
         }
         return nullptr;
     }
@@ -1043,12 +836,14 @@ static FwdKernel pick(int kern, int mrows, int tn) {
 }
 
 static FwdKernel pick_kernel(int kern, int mrows, int tn, bool symmetric) {
+    if (kern == kKernMid) return pick_mid(mrows, tn, symmetric);
     return symmetric ? pick<true>(kern, mrows, tn) : pick<false>(kern, mrows, tn);
 }
 
 const char *kernel_name(int kern, int mrows, int tn, bool symmetric) {
     static thread_local char buf[64];
     if (kern == kKernTiled) snprintf(buf, sizeof buf, "k_tiled<%d,%d%s>", mrows / 16, tn, symmetric ? ",sym" : "");
+    else if (kern == kKernMid) snprintf(buf, sizeof buf, "k_mid<%d,%d%s>", mrows / 16, tn, symmetric ? ",sym" : "");
     else if (kern == kKernMfma16) snprintf(buf, sizeof buf, "k_mfma16<%d%s>", tn, symmetric ? ",sym" : "");
     else if (kern == kKernGemv) snprintf(buf, sizeof buf, "k_gemv4<%d,%d%s>", mrows, tn, symmetric ? ",sym" : "");
     else snprintf(buf, sizeof buf, "k_skinny<%d,%d%s>", mrows / 16, tn, symmetric ? ",sym" : "");
@@ -1064,7 +859,11 @@ hipError_t prepare_kernels() {
                 (void)hipFuncSetAttribute((const void *)pick_kernel(kKernGemv, mv, tn, sym),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
         }
-        for (int xr : {1, 2, 4, 8, 16, 32, 48, 64})
+        for (int mt = 2; mt <= 4; ++mt)
+            for (int tn = 1; tn <= mid_tiles_max(mt); ++tn)
+                (void)hipFuncSetAttribute((const void *)pick_mid(16 * mt, tn, sym),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+        for (int xr : {1, 2, 4, 8, 16})
             (void)hipFuncSetAttribute((const void *)pick_kernel(kKernStaged, 0, xr, sym),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
     }

@@ -26,8 +26,9 @@ struct qlin_s {
     int64_t K = 0, N = 0;
     int Kb = 0, Nt = 0;
     bool symmetric = false;
+    bool f16 = false;            // dequantization route: codes as f16 subnormals (device_common.h)
     uint4 *codes = nullptr;      // Nt * Kb blocks of 1 KiB
-    void *sz = nullptr;          // Nt * Kb * 16 entries (u32 s|z<<16, or u16 s)
+    void *sz = nullptr;          // Nt * Kb * 16 entries (u32 words of s and z, or u16 s)
     // Workspace of qlin_forward / qlin_forward_path: arrival counters, then
     // fp32 split-K partials, sized at creation for the plans qlin_forward
     // runs at M <= 16 (zero bytes when none of them cuts the K range).
@@ -129,6 +130,19 @@ int check_scales(const uint16_t *s, size_t n) {
                         (unsigned)s[i]);
     }
     return QLIN_OK;
+}
+
+// Do all scales lie in [2^-25, 2^4)?  There s 2^12 and, for the columns whose
+// codes sit four bits higher, s 2^8 are exact f16 numbers (down to the last
+// subnormal bit at 2^-25, below 65504 at the top), which is what the f16
+// dequantization route needs; the 4096-fold smaller sums stay far from
+// binary32's subnormals.  Other handles take the bf16 route.
+bool scales_fit_f16(const uint16_t *s, size_t n) {
+    for (size_t i = 0; i < n; ++i) {
+        const int e = ((s[i] >> 7) & 0xFF) - 127;
+        if (e < -25 || e > 3) return false;
+    }
+    return true;
 }
 
 int check_zeros(const uint16_t *z, size_t n) {
@@ -301,6 +315,19 @@ int gemv_max_auto() {
     return v;
 }
 
+// Estimated time (ns) of a k_mid launch, fitted to every split from 1 to 8 of the decoder's
+// linears at 17 to 64 rows (within 10% where a plan is chosen): per round of 8
+// groups the x of the waves and the blocks of the tiles, per tile the sums at
+// the end, and for a split the partial sums written and read back.
+double mid_cost(const Target &t, int M, int S, int Gn, int Tn) {
+    const int mt = (M + 15) / 16, Kc = (t.Kb + S - 1) / S, rem = Kc % kWaves;
+    const double passes = (double)((S * Gn + t.num_cu - 1) / t.num_cu);
+    const double rounds = Kc / kWaves + (rem == 0 ? 0.0 : 2 * rem <= kWaves ? 0.5 : 1.0);
+    double c = 1900.0 + passes * (rounds * (200.0 + 330.0 * mt + Tn * (360.0 + 70.0 * mt)) + 190.0 * mt * Tn);
+    if (S > 1) c += 1300.0 + S * (100.0 + (double)M * t.N * 8.0 * 0.5e-3);
+    return c;
+}
+
 // Estimated time (ns) of one launch, fitted to measurements on MI355X:
 // a fixed part (launch, first HBM round trip, the staged kernel's x
 // staging barrier), the blocks of the busiest workgroup, the staged x
@@ -308,6 +335,7 @@ int gemv_max_auto() {
 // range is cut.  The register-resident kernel reloads x per group and
 // wave, which costs more per block as M grows.
 double plan_cost(const Target &t, int kern, int M, int S, int Gn, int Tn) {
+    if (kern == kKernMid) return mid_cost(t, M, S, Gn, Tn);
     const int Kc = (t.Kb + S - 1) / S;
     const int rounds = (S * Gn + t.num_cu - 1) / t.num_cu;
     const double blocks = (double)rounds * Tn * Kc;
@@ -501,10 +529,12 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
     if (path == kGemv) kerns[nk++] = kKernGemv;
     else if (path == kRegs) kerns[nk++] = kKernMfma16;
     else if (auto_pick && Mi <= 16) { kerns[nk++] = kKernMfma16; kerns[nk++] = kKernStaged; }
-    else kerns[nk++] = kKernStaged;
+    else kerns[nk++] = Mi <= 16 ? kKernStaged : kKernMid;
 
     auto tn_max_of = [&](int kern) {
-        return kern == kKernGemv ? kTnMaxGemv : kern == kKernMfma16 ? kTnMax : t.Nt;
+        return kern == kKernGemv ? kTnMaxGemv
+               : kern == kKernMfma16 ? kTnMax
+               : kern == kKernMid ? mid_tiles_max((Mi + 15) / 16) : t.Nt;
     };
     auto rows_of = [&](int kern) { return kern == kKernGemv ? Mi : 16 * ((Mi + 15) / 16); };
     // widest range of (kern, S, Gn) if the split fits, else -1
@@ -514,6 +544,12 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         const int Kc = (t.Kb + S - 1) / S;
         if (S > 1 && ((size_t)S * Gn * Tn * Mi * 16 > t.cap_floats || Gn > t.cap_counters)) return -1;
         if (Tn > tn_max_of(kern)) return -1;
+        if (kern == kKernMid) {
+            // a forced split keeps the limit it is documented with: its chunk
+            // of x must fit LDS (the automatic plans have no such limit)
+            if (split_k > 0 && !chunk_fits(Mi, Kc)) return -1;
+            return (int64_t)Tn * t.Kb * 1024 < ((int64_t)1 << 31) ? Tn : -1;   // span of its descriptors
+        }
         if (kern != kKernStaged) return lds_bytes_regs(rows_of(kern), Tn) <= kLdsMax ? Tn : -1;
         if (!chunk_fits(Mi, Kc)) return -1;
         if ((int64_t)Tn * Kc >= 65536) return -1;   // the kernel's block walk divides u < 2^16 by Kc
@@ -532,6 +568,8 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         lo = std::max(lo, need);
         int Gn = std::max(lo, std::min(t.Nt, std::max(1, t.num_cu / S)));
         Gn = std::min(Gn, t.Nt);
+        // S chunks of every column must fit the workspace whatever Gn is
+        if (S > 1 && (size_t)S * t.Nt * Mi * 16 > t.cap_floats) return Gn;
         while (Gn < t.Nt && fits(kern, S, Gn) < 0) ++Gn;
         return Gn;
     };
@@ -567,6 +605,16 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         if (split_k > 0) return fail(QLIN_ERR_UNSUPPORTED, "split_k=%d does not fit (LDS or workspace)", (int)split_k);
         return fail(QLIN_ERR_UNSUPPORTED, "no work split fits this shape and workspace");
     }
+    // Past 48 rows with every workgroup at k_mid's tile limit, a caller's
+    // workspace that holds three chunks takes the tiled kernel's K split
+    if (auto_pick && bestK == kKernMid && bestS == 1 && Mi > 48 && bestTn == mid_tiles_max(4) && t.Kb >= 3) {
+        Plan q;
+        if (make_tiled_plan(t, 3, Mi, &q) == QLIN_OK) {
+            *p = q;
+            return QLIN_OK;
+        }
+        clear_err();
+    }
     p->kern = bestK;
     p->mrows = rows_of(bestK);
     p->S = bestS;
@@ -574,10 +622,11 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
     p->TnMax = bestTn;
     p->grid = bestS * bestGn;
     split_ranges(t, bestGn, bestTn, p->gn);
-    const bool regs = bestK != kKernStaged;
     const int Kc = (t.Kb + bestS - 1) / bestS;
-    p->tn = regs ? bestTn : staged_rows(Mi);
-    const size_t need = regs ? lds_bytes_regs(p->mrows, bestTn) : lds_bytes(Mi, Kc, bestTn);
+    p->tn = bestK == kKernStaged ? staged_rows(Mi) : bestTn;
+    const size_t need = bestK == kKernStaged ? lds_bytes(Mi, Kc, bestTn)
+                        : bestK == kKernMid  ? mid_lds_bytes(p->mrows / 16)
+                                             : lds_bytes_regs(p->mrows, bestTn);
     // at least 80 KiB + 1 of LDS per workgroup keeps one workgroup per CU, so
     // the grid spreads over all CUs
     p->lds = std::max(need, (size_t)80 * 1024 + 256);
@@ -638,6 +687,7 @@ FwdArgs fwd_args(const Target &t, const Plan &p, int64_t M, const uint16_t *x, u
         f.sz = h->sz;
         f.y = ys[i] + row0 * h->N;
         f.N = (int)h->N;
+        f.f16 = h->f16 ? 1 : 0;
         f.Nq = h->Nt / p.gn[i];
         f.Nr = h->Nt % p.gn[i];
         a.gn0[i] = gn0;
@@ -702,6 +752,7 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
     a.ws = ws_partials(ws);
     a.ws_bytes = ws_partial_bytes(ws, ws_bytes);
     a.nmem = t.nmem;
+    a.f16 = 0;
     int gb0 = 0;
     for (int i = 0; i < kMaxMembers; ++i) {
         TiledMember &f = a.mem[i];
@@ -716,6 +767,7 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
         f.y = ys[i];
         f.N = (int)h->N;
         f.Nt = h->Nt;
+        if (h->f16) a.f16 |= 1u << i;
         a.gb0[i] = gb0;
         gb0 += (h->Nt + 4 * p.tn - 1) / (4 * p.tn);
     }
@@ -729,17 +781,18 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
 // caller.
 int launch_all(const Target &t, int path, int64_t split_k, int64_t M, const uint16_t *x, uint16_t *const *ys,
                void *ws, size_t ws_bytes, hipStream_t st) {
-    const bool tiled = path == kTiled || (path == kAuto && auto_tiled(M));
+    // rows left over by launches of a tiled plan stay with the tiled kernel
+    const int rest = path == kAuto && auto_tiled(M) ? kTiled : path;
     for (int64_t m0 = 0; m0 < M;) {
         Plan p;
-        int rc = tiled ? make_tiled_plan(t, split_k, M - m0, &p) : make_plan(t, path, split_k, M - m0, &p);
+        int rc = make_plan(t, rest, split_k, M - m0, &p);
         if (rc != QLIN_OK) return rc;
         const int64_t Ms = std::min<int64_t>(p.rows, M - m0);
         if (Ms != p.rows) {
-            rc = tiled ? make_tiled_plan(t, split_k, Ms, &p) : make_plan(t, path, split_k, Ms, &p);
+            rc = make_plan(t, rest, split_k, Ms, &p);
             if (rc != QLIN_OK) return rc;
         }
-        if (tiled) {
+        if (p.kern == kKernTiled) {
             uint16_t *yk[kMaxMembers];
             for (int i = 0; i < t.nmem; ++i) yk[i] = ys[i] + m0 * t.mem[i]->N;
             if ((rc = launch_tiled_rows(t, p, Ms, x + m0 * t.K, yk, ws, ws_bytes, st)) != QLIN_OK) return rc;
@@ -811,6 +864,7 @@ qlin_t create_impl(int64_t K, int64_t N, int64_t group, const uint32_t *packed, 
     h->Kb = (int)(K / kGroup);
     h->Nt = (int)(N / kTileN);
     h->symmetric = symmetric;
+    h->f16 = scales_fit_f16(s_host.empty() ? scales : s_host.data(), ngroups);
     const size_t code_bytes = (size_t)N * K / 2;
     const size_t sz_bytes = ngroups * (symmetric ? 2 : 4);
 
@@ -867,7 +921,7 @@ qlin_t create_impl(int64_t K, int64_t N, int64_t group, const uint32_t *packed, 
     // set-up of this device's static scratch (qlin_forward_group_noalloc), once
     if ((e = static_scratch_setup(h->device, st)) != hipSuccess) return bail("static scratch set-up", e);
     if ((e = launch_repack((const uint32_t *)canon, (const uint16_t *)sc, (const uint16_t *)zc, h->codes, h->sz,
-                           (int)K, (int)N, symmetric, st)) != hipSuccess)
+                           (int)K, (int)N, symmetric, h->f16, st)) != hipSuccess)
         return bail("repack launch", e);
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return bail("repack", e);
     (void)hipStreamDestroy(st);
@@ -894,7 +948,7 @@ int run_forward(qlin_s *h, int path, int64_t split_k, int64_t M, const uint16_t 
     if (path == kGemv && M > kMaxGemvM) return fail(QLIN_ERR_UNSUPPORTED, "GEMV path needs M <= %d", kMaxGemvM);
     const hipStream_t st = (hipStream_t)stream;
     const CachedPlan *cp = (path == kAuto && split_k == 0 && M <= kMaxSkinnyM) ? &h->auto_plans[M - 1] : nullptr;
-    if (cp && cp->ok && cp->p.rows >= M) {     // the automatic plan, computed at creation: one launch
+    if (cp && cp->ok && cp->p.rows >= M && cp->p.kern != kKernTiled) {     // the automatic plan, computed at creation: one launch
         const FwdArgs a = fwd_args(t, cp->p, M, x, ys, h->ws, h->ws_bytes, 0);
         const hipError_t e = launch_forward(cp->p.kern, cp->p.mrows, cp->p.tn, t.symmetric, cp->p.grid, cp->p.lds, a, st);
         if (e != hipSuccess) return hip_fail(e, "forward launch");
@@ -951,7 +1005,7 @@ int plan_text(const Target &t, int path, int64_t split_k, int64_t M, char *buf, 
     if (rc != QLIN_OK) return rc;
     const bool tiled = p.kern == kKernTiled;
     const int64_t launches = (M + p.rows - 1) / p.rows;
-    static const char *names[] = {"gemv", "regs", "skinny", "tiled"};
+    static const char *names[] = {"gemv", "regs", "skinny", "tiled", "skinny"};
     snprintf(buf, (size_t)buflen, "path=%s kernel=%s grid=%d block=%d split=%d ranges=%d lds=%zu launches=%lld",
              names[p.kern], kernel_name(p.kern, p.mrows, p.tn, t.symmetric), p.grid,
              tiled ? kTiledWaves * 64 * tiled_wsplit(TiledShape{p.mrows / 16, p.tn}) : kThreads, p.S, p.Gn, p.lds,
@@ -1093,7 +1147,7 @@ int qlin_dequantize(qlin_t h, int routine, uint16_t *w_out, void *stream) {
     if (!h || !w_out) return fail(QLIN_ERR_INVALID, "NULL argument");
     if (routine != 0 && routine != 1) return fail(QLIN_ERR_INVALID, "routine must be 0 or 1");
     if ((uintptr_t)w_out & 15) return fail(QLIN_ERR_ALIGN, "w_out must be 16-byte aligned");
-    hipError_t e = launch_dequant(routine, h->codes, h->sz, h->symmetric, w_out, (int)h->K, (int)h->N,
+    hipError_t e = launch_dequant(routine, h->codes, h->sz, h->symmetric, h->f16, w_out, (int)h->K, (int)h->N,
                                   (hipStream_t)stream);
     return e == hipSuccess ? QLIN_OK : hip_fail(e, "dequantize launch");
 }

@@ -33,6 +33,7 @@ enum Kern {
     kKernGemv = 0,     // k_gemv4: M <= 4, group-major walk, x in registers (GEMV path)
     kKernMfma16 = 1,   // k_mfma16: M <= 16, group-major walk, x in registers (REGS path)
     kKernStaged = 2,   // k_skinny<MT>: M <= 64, tile-major walk, x chunk staged in LDS (SKINNY path)
+    kKernMid = 4,      // k_mid<MT, TN>: 17 <= M <= 64, K cut over the waves, whole groups each (SKINNY path)
     kKernTiled = 3     // k_tiled: any M, 128 x 256 output blocks, x and weights staged in LDS (TILED path)
 };
 
@@ -46,10 +47,11 @@ enum Kern {
 constexpr int kMaxMembers = 8;
 struct FwdMember {
     const uint4 *codes;     // device layout, Nt * Kb blocks of 1 KiB
-    const void *sz;         // per (tile, group, column): u32 s | zc << 16 with zc = -(128 + z), or u16 s (symmetric)
+    const void *sz;         // per (tile, group, column): the 32-bit word of s and z, or 16 bits of s (symmetric)
     uint16_t *y;            // [M][N] bf16
     int N;                  // output columns
     int Nq, Nr;
+    int f16;                // the handle's dequantization route (device_common.h)
 };
 struct FwdArgs {
     const uint16_t *x;      // [M][K] bf16, shared by all members
@@ -99,6 +101,7 @@ struct TiledArgs {
     uint32_t *counters;     // S > 1: [Gn Mt] arrival counters, zero between launches
     uint32_t ws_bytes;      // size of ws
     int nmem;
+    uint32_t f16;           // bit i: dequantization route of member i (device_common.h)
     int gb0[kMaxMembers];   // first column block of each member (Gn for absent members)
     TiledMember mem[kMaxMembers];
 };
@@ -127,13 +130,22 @@ inline size_t lds_bytes(int M, int Kc, int Tn) {
     return x + (size_t)kWaves * Tn * mrows * 16 * 4;
 }
 
+// k_mid (mid.hip) with mt m-tiles of 16 rows: most column tiles per workgroup
+// (4 mt accumulator registers each) and LDS bytes: 16 mt rows x 256 bytes of x
+// per wave (the four partial sums per tile that take their place need no more).
+constexpr int mid_tiles_max(int mt) { return mt == 2 ? 8 : mt == 3 ? 6 : 5; }
+constexpr size_t mid_lds_bytes(int mt) { return (size_t)kWaves * mt * 4096; }
+static_assert(4 * 8 * 1024 <= kWaves * 4096, "partial sums of 8 tiles fit where x was");
+typedef void (*FwdKernel)(FwdArgs);
+FwdKernel pick_mid(int mrows, int tn, bool symmetric);
+
 // Host launchers (kernels.hip).  Each returns the launch status.
 hipError_t launch_repack(const uint32_t *canon, const uint16_t *scales, const uint16_t *zeros,
-                         uint4 *codes, void *sz, int K, int N, bool symmetric, hipStream_t st);
+                         uint4 *codes, void *sz, int K, int N, bool symmetric, bool f16, hipStream_t st);
 hipError_t launch_forward(int kern, int mrows, int tn, bool symmetric, int grid, size_t lds,
                           const FwdArgs &a, hipStream_t st);
 hipError_t launch_unpack(const uint4 *codes, uint8_t *q, int K, int N, hipStream_t st);
-hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool symmetric,
+hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool symmetric, bool f16,
                           uint16_t *w, int K, int N, hipStream_t st);
 hipError_t prepare_kernels();     // per-process attribute setup (LDS limits)
 hipError_t launch_quantize(const uint16_t *w, const uint16_t *scales, const uint16_t *zeros, uint32_t *packed,

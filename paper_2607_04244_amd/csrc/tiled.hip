@@ -9,6 +9,7 @@
 
 #include "device_common.h"
 
+#include <type_traits>
 
 namespace qlin {
 
@@ -69,7 +70,6 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     __shared__ __align__(16) uint32_t ws_sz[kTiledStages][kTiles * 64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ExtractConsts kx;
     // block index -> (column block jn, row block im, K chunk c): XCD x (=
     // block index mod 8) takes an equal contiguous slice of the Gn Mt S work
     // items in column-block-major order, in dispatch order
@@ -123,7 +123,6 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     const int g0 = SPLIT ? c * a.Kq + min(c, a.Kr) : 0;   // the chunk's groups [g0, g1]
     const int g1 = SPLIT ? g0 + a.Kq + (c < a.Kr ? 1 : 0) - 1 : a.Kb - 1;
     const int lm = lane & 15, lg = lane >> 4;
-    const DiagSel dsel(lane);
 
     // All global reads are direct-to-LDS buffer loads issued through inline
     // assembly (load_lds_buf16 / load_lds_buf4): the compiler does not track
@@ -158,7 +157,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     // blocks span at most 16 Kb KiB); wv / sv = byte offsets of this lane's
     // part of block (tile, 0)
     const int t0 = (jn - gb) * kTiles, ntw = min(kTiles, Nt - t0);
-    constexpr uint32_t kSzBlk = SYM ? kTileN * 2 : kTileN * 4;          // s|z bytes per block
+    constexpr uint32_t kSzBlk = kTileN * (SYM ? kSzBytesSym : kSzBytesAsym);          // s|z bytes per block
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)(f.codes + (size_t)t0 * a.Kb * 64), 0, ntw * a.Kb * 1024, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
@@ -168,7 +167,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     for (int u = 0; u < NW; ++u) {
         const uint32_t tr = (uint32_t)(min(t0 + wave * NW + u, Nt - 1) - t0) * (uint32_t)a.Kb;   // block (tile, 0)
         wv[u] = tr * 1024u + lane * 16u;
-        // 2-byte scales: one dword per lane covers columns 2i, 2i + 1 (read_w picks the half)
+        // 2-byte scales: one dword per lane covers columns 2i, 2i + 1
         sv[u] = tr * kSzBlk + (SYM ? (lane & 7) : lm) * 4u;
     }
     constexpr uint32_t kWStage = kTiles * 64 * 16, kSStage = kTiles * 64 * 4;
@@ -186,12 +185,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
         for (int t = 0; t < NW; ++t) {
             const int slot = (wave * NW + t) * 64;
             cw[t] = ws_codes[buf][slot + lane];
-            if constexpr (SYM) {
-                const uint32_t pair = ws_sz[buf][slot + (lm >> 1)];
-                sw[t] = ((lm & 1) ? (pair >> 16) : (pair & 0xFFFFu)) | (kZcSymmetric << 16);
-            } else {
-                sw[t] = ws_sz[buf][slot + lm];
-            }
+            sw[t] = ws_sz[buf][slot + (SYM ? lm >> 1 : lm)];
         }
     };
 
@@ -204,10 +198,12 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     // LDS slot of this lane's operand read: row 16 ms + lm, chunk 4 j + lg
     auto xslot = [&](int ms, int j) { return ms * 256 + lm * 16 + ((4 * j + lg) ^ lm); };
 
-    auto compute = [&](int buf, const uint4 (&cw)[NW], const uint32_t (&sw)[NW]) {
+    // one step's products; the K walk below exists once per dequantization
+    // route (uniform in the workgroup: its tiles belong to one member)
+    auto compute = [&](const auto &kx, const auto &dsel, int buf, const uint4 (&cw)[NW], const uint32_t (&sw)[NW]) {
         MfmaDeq d[NW];
 #pragma unroll
-        for (int t = 0; t < NW; ++t) d[t] = mfma_setup(sw[t], dsel);
+        for (int t = 0; t < NW; ++t) d[t] = dsel.setup(sw[t]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             v8bf wa[NW];
@@ -247,27 +243,35 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
         load_x(min(g0 + i, g1), i);
         load_w(min(g0 + i, g1), i);
     }
-    int buf = 0;
-    for (int kb = g0; kb <= g1; ++kb) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * kIssued) : "memory");
-        uint4 cw[NW];
-        uint32_t sw[NW];
-        read_w(buf, cw, sw);
-        const int nb = buf == 0 ? S - 1 : buf - 1;             // (kb - g0 + S - 1) % S
-        if constexpr (MSW >= 6) {
-            // the wave's own blocks in nb were read (and waited for) in the
-            // previous step: their refill can go out before the barrier
-            load_w(min(kb + S - 1, g1), nb);
-            lds_barrier();                    // group kb is in LDS for every wave; buffer nb is free
-            load_x(min(kb + S - 1, g1), nb);
-        } else {
-            lds_barrier();
-            load_x(min(kb + S - 1, g1), nb);
-            load_w(min(kb + S - 1, g1), nb);
+    auto walk = [&](auto route) {
+        constexpr bool F16 = decltype(route)::value;
+        const ExtractConsts<F16> kx;
+        const DeqSel<SYM, F16> dsel(lane);
+        int buf = 0;
+        for (int kb = g0; kb <= g1; ++kb) {
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * kIssued) : "memory");
+            uint4 cw[NW];
+            uint32_t sw[NW];
+            read_w(buf, cw, sw);
+            const int nb = buf == 0 ? S - 1 : buf - 1;             // (kb - g0 + S - 1) % S
+            if constexpr (MSW >= 6) {
+                // the wave's own blocks in nb were read (and waited for) in the
+                // previous step: their refill can go out before the barrier
+                load_w(min(kb + S - 1, g1), nb);
+                lds_barrier();                    // group kb is in LDS for every wave; buffer nb is free
+                load_x(min(kb + S - 1, g1), nb);
+            } else {
+                lds_barrier();
+                load_x(min(kb + S - 1, g1), nb);
+                load_w(min(kb + S - 1, g1), nb);
+            }
+            compute(kx, dsel, buf, cw, sw);
+            buf = buf == S - 1 ? 0 : buf + 1;
         }
-        compute(buf, cw, sw);
-        buf = buf == S - 1 ? 0 : buf + 1;
-    }
+    };
+    const bool f16 = (a.f16 >> m) & 1u;
+    if (f16) walk(std::true_type{});
+    else walk(std::false_type{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the reloads past the end
 
     if constexpr (SPLIT) {
@@ -331,6 +335,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     }
 
     // D of the 16x16 op: lane l holds rows n = 4 (l >> 4) + v of column m = l & 15
+    const float unscale = f16 ? kF16Unscale : 1.0f;
 #pragma unroll
     for (int ms = 0; ms < MSW; ++ms) {
         const int row = im * BM + ms * 16 + lm;
@@ -340,7 +345,8 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
             const int tt = t0 + wave * NW + t;
             if (tt >= Nt) continue;
             const v4f v = acc[ms][t];
-            const uint2 o = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+            const uint2 o = make_uint2(cvt_pk_bf16(v[0] * unscale, v[1] * unscale),
+                                       cvt_pk_bf16(v[2] * unscale, v[3] * unscale));
             *(uint2 *)(f.y + (size_t)row * f.N + (size_t)tt * kTileN + 4 * lg) = o;
         }
     }

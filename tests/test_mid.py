@@ -1,0 +1,97 @@
+"""GPU tests of the 17 to 64 row kernel and of the two dequantization routes
+(needs an MI355X): the sizes where a workgroup's rounds, tiles and rows end
+unevenly, and the ends of the scale range that each route takes, against the
+oracle within max(2 bf16 ulp, 1e-3); integer sums and dequantized weights bit
+for bit.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import qlin_ref as ref
+from paper_2607_04244_amd import qlin
+from synth import gen
+
+from test_parity import assert_close, dev, host_bits, make, oracle, run
+
+pytestmark = pytest.mark.gpu
+
+SKINNY, AUTO = qlin.PATH_SKINNY, qlin.PATH_AUTO
+
+
+@pytest.mark.parametrize("M", [17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("Kb,N", [(1, 16), (4, 48), (5, 16), (8, 208), (9, 32), (12, 16), (13, 80), (20, 12304),
+                                  (3, 20480)])
+def test_rounds_tiles_and_rows_end_unevenly(M, Kb, N):
+    """Groups below, at and past the 8 of a round (the last up to four shared
+    by two waves each), one to the most tiles a workgroup holds, full and
+    partial m-tiles; both formats, without a K split."""
+    for sym in (False, True):
+        c = gen.random_case(M * 1000 + Kb * 10 + N + sym, M, 128 * Kb, N)
+        lin = make(c, symmetric=sym)
+        assert "kernel=k_mid" in lin.plan(M), lin.plan(M)
+        assert_close(run(lin, c["x"], SKINNY), oracle(c, symmetric=sym), f"M={M} Kb={Kb} N={N} sym={sym}")
+        lin.close()
+
+
+@pytest.mark.parametrize("M,split", [(17, 2), (33, 3), (64, 5)])
+def test_split_integer_sums_are_bit_exact(M, split):
+    K, N = 128 * 21, 176
+    rng = np.random.default_rng(M)
+    Q = rng.integers(0, 16, size=(N, K), dtype=np.uint8)
+    xi = rng.integers(-1, 2, size=(M, K))
+    x = np.select([xi == 1, xi == -1], [0x3F80, 0xBF80], 0).astype(np.uint16)
+    c = dict(K=K, N=N, packed=ref.pack_codes(Q), scales=np.full((N, K // 128), 0x3F80, np.uint16))
+    lin = make(c, symmetric=True)
+    y_ref = ref.round_output(ref.forward(x, c["packed"], c["scales"], ref.symmetric_zeros(N, K)))
+    for _ in range(2):                     # the arrival counters are left at zero
+        assert np.array_equal(run(lin, x, SKINNY, split), y_ref)
+    lin.close()
+
+
+# bf16 scales at the ends of the f16 route's range [2^-25, 2^4) and just past them
+F16_LO, F16_HI = (127 - 25) << 7, (127 + 3) << 7 | 127
+
+
+@pytest.mark.parametrize("lo,hi", [(F16_LO, F16_LO + 127), (F16_LO, F16_HI), (F16_LO - 1, F16_HI), (F16_LO, F16_HI + 1),
+                                   (27 << 7, 226 << 7)])
+@pytest.mark.parametrize("sym", [False, True])
+def test_scale_range_of_both_routes(lo, hi, sym):
+    """Dequantized weights bit for bit through both routines, and sums through
+    every decode kernel, for scales spread over [lo, hi] (bf16 patterns) with
+    both ends present and every zero-point in [0, 15].  x is scaled so that the
+    outputs are of the order of one."""
+    K, N = 512, 64
+    rng = np.random.default_rng(lo + hi)
+    scales = rng.integers(lo, hi + 1, size=(N, K // 128)).astype(np.uint16)
+    scales[0, 0], scales[N - 1, K // 128 - 1] = lo, hi
+    packed = rng.integers(0, 2 ** 32, size=(N, K // 8), dtype=np.uint32)
+    zeros = gen.f32_to_bf16_bits(rng.integers(0, 16, size=(N, K // 128)).astype(np.float32))
+    z = ref.symmetric_zeros(N, K) if sym else zeros
+    lin = qlin.QLinear(packed, scales, None if sym else zeros)
+    w = ref.dequant_bf16(packed, scales, z)
+    for routine in (0, 1):
+        assert np.array_equal(host_bits(lin.dequantize(routine)), w), f"routine {routine}"
+    top = float(ref.bf16_to_f64(np.array([hi], np.uint16))[0])
+    x = gen.f32_to_bf16_bits((rng.standard_normal((40, K)) / (8.0 * top)).astype(np.float32))
+    for path, M in ((qlin.PATH_GEMV, 3), (qlin.PATH_REGS, 16), (SKINNY, 16), (SKINNY, 40), (qlin.PATH_TILED, 40)):
+        assert_close(run(lin, x[:M], path), ref.forward(x[:M], packed, scales, z), f"path={path} M={M}")
+    lin.close()
+
+
+@pytest.mark.parametrize("M", [1, 16, 40, 130])
+def test_group_of_both_routes(M):
+    """One launch over members whose scales take different routes."""
+    K = 640
+    cases = [gen.random_case(700 + i, M, K, N, s_range=r) for i, (N, r) in
+             enumerate(((48, (0.002, 0.02)), (272, (20.0, 40.0)), (16, (0.002, 0.02))))]
+    lins = [make(c) for c in cases]
+    x = cases[0]["x"]
+    need, _ = qlin.group_plan(lins, M)
+    ys = qlin.forward_group(lins, dev(x), workspace=qlin.new_workspace(need) if need else None)
+    torch.cuda.synchronize()
+    for c, y in zip(cases, ys):
+        assert_close(host_bits(y), oracle(dict(c, x=x)), f"M={M} N={c['N']}")
+    for l in lins:
+        l.close()
