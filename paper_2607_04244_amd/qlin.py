@@ -158,7 +158,7 @@ def quantize(w, scales, zeros=None, group=128):
     packed = torch.empty((N, K // 8), dtype=torch.int32, device=w.device)
     zp = zeros.contiguous().data_ptr() if zeros is not None else None
     _check(qlin_quantize(K, N, group, w.data_ptr(), scales.contiguous().data_ptr(), zp, packed.data_ptr(),
-                         torch.cuda.current_stream().cuda_stream))
+                         _stream()))
     return packed
 
 
@@ -246,6 +246,21 @@ def qlin_swa_attention(Hq, Hkv, head_dim, nq, T, kv_stride, window, splits, q_pt
 
 # ---------------------------------------------------------------- torch wrappers
 
+_raw_stream = _current_device = None
+
+
+def _stream():
+    """The current stream of the current device, as an integer (for callers
+    that hold a CUDA tensor or a handle, so CUDA is initialised).  torch's raw
+    getters: building a torch.cuda.Stream object to ask it for its pointer
+    takes 2.5 us, a quarter of a small call; the getters take 0.1 us."""
+    global _raw_stream, _current_device
+    if _raw_stream is None:
+        import torch
+        _current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    return _raw_stream(_current_device())
+
+
 def swa_attention(q, k, v, window, T=None, splits=0, out=None, workspace=None):
     """Drafter block attention with a symmetric window (include/qlin_attn.h).
 
@@ -265,16 +280,18 @@ def swa_attention(q, k, v, window, T=None, splits=0, out=None, workspace=None):
     if k.device != q.device or v.device != q.device:
         raise ValueError("q, k and v must be on one device")
     T = cap if T is None else T
-    S, ws_bytes, _ = qlin_swa_plan(Hq, Hkv, D, nq, T, window, splits)
+    if workspace is None:                        # with one given, the call itself checks sizes and plan
+        _, ws_bytes, _ = qlin_swa_plan(Hq, Hkv, D, nq, T, window, splits)
+        if ws_bytes:
+            workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
     if out is None:
         out = torch.empty((Hq, nq, D), dtype=torch.bfloat16, device=q.device)
-    _check_out(out, (Hq, nq, D), q.device)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=q.device)
+    else:
+        _check_out(out, (Hq, nq, D), q.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(qlin_swa_attention(Hq, Hkv, D, nq, T, cap, window, splits, q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                              out.data_ptr(), ws_ptr, ws_len, torch.cuda.current_stream().cuda_stream))
+                              out.data_ptr(), ws_ptr, ws_len, _stream()))
     return out
 
 
@@ -304,11 +321,12 @@ def forward_group(lins, x, outs=None, path=PATH_AUTO, split_k=0, workspace=None)
     M = x.shape[0]
     if outs is None:
         outs = [torch.empty((M, l.N), dtype=torch.bfloat16, device=x.device) for l in lins]
-    for l, o in zip(lins, outs):
-        _check_out(o, (M, l.N), x.device)
+    else:
+        for l, o in zip(lins, outs):
+            _check_out(o, (M, l.N), x.device)
     wp, wb = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) if workspace is not None else (None, 0)
     _check(qlin_forward_group([l.h for l in lins], path, split_k, M, x.data_ptr(), [o.data_ptr() for o in outs],
-                              wp, wb, torch.cuda.current_stream().cuda_stream))
+                              wp, wb, _stream()))
     return outs
 
 
@@ -337,10 +355,6 @@ class QLinear:
         else:
             self.h = qlin_create(self.K, self.N, group, packed, scales, zeros)
 
-    def _stream(self):
-        import torch
-        return torch.cuda.current_stream().cuda_stream
-
     def _check_x(self, x):
         import torch
         if x.dtype != torch.bfloat16 or x.device != self.device or x.dim() != 2 or x.shape[1] != self.K:
@@ -355,9 +369,12 @@ class QLinear:
             return forward_group([self], x, None if out is None else [out], path, split_k, workspace)[0]
         x = self._check_x(x)
         M = x.shape[0]
-        y = out if out is not None else torch.empty((M, self.N), dtype=torch.bfloat16, device=x.device)
-        _check_out(y, (M, self.N), x.device)
-        _check(qlin_forward_path(self.h, path, split_k, M, x.data_ptr(), y.data_ptr(), self._stream()))
+        if out is None:
+            y = torch.empty((M, self.N), dtype=torch.bfloat16, device=x.device)
+        else:
+            y = out
+            _check_out(y, (M, self.N), x.device)
+        _check(qlin_forward_path(self.h, path, split_k, M, x.data_ptr(), y.data_ptr(), _stream()))
         return y
 
     __call__ = forward
@@ -372,13 +389,13 @@ class QLinear:
     def unpack_codes(self):
         import torch
         q = torch.empty((self.N, self.K), dtype=torch.uint8, device="cuda")
-        _check(qlin_unpack_codes(self.h, q.data_ptr(), self._stream()))
+        _check(qlin_unpack_codes(self.h, q.data_ptr(), _stream()))
         return q
 
     def dequantize(self, routine=0):
         import torch
         w = torch.empty((self.N, self.K), dtype=torch.bfloat16, device="cuda")
-        _check(qlin_dequantize(self.h, routine, w.data_ptr(), self._stream()))
+        _check(qlin_dequantize(self.h, routine, w.data_ptr(), _stream()))
         return w
 
     def close(self):
