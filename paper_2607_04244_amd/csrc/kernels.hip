@@ -859,7 +859,7 @@ hipError_t prepare_kernels() {
                 (void)hipFuncSetAttribute((const void *)pick_kernel(kKernGemv, mv, tn, sym),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
         }
-        for (int mt = 2; mt <= 4; ++mt)
+        for (int mt = 2; mt <= kMidTilesM; ++mt)
             for (int tn = 1; tn <= mid_tiles_max(mt); ++tn)
                 (void)hipFuncSetAttribute((const void *)pick_mid(16 * mt, tn, sym),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);

@@ -1,4 +1,4 @@
-// 17 to 64 rows: the W4A16 linear for a few draft blocks at once, CDNA4 (gfx950).
+// 17 to 144 rows: the W4A16 linear for a few draft blocks at once, CDNA4 (gfx950).
 //
 // Same layer as the other decode kernels (Sec. 2.1, 3.2, 3.3 of arXiv
 // 2607.04244).  This file is compiled with matrix-core results kept in
@@ -13,76 +13,89 @@ namespace qlin {
 // A workgroup owns K chunk c (groups [g0, g0 + Kc)) of column tiles
 // [t0, t0 + Tn), Tn <= TN, and all 16 MT rows: every weight of the launch is
 // read and dequantized exactly once.  Its 8 waves cut the K range: in a round
-// each takes one whole group and there all of the workgroup's tiles, so the x
-// it needs (16 MT rows x 128 k) is read from LDS into registers once and
+// each takes one unit of K and there all of the workgroup's tiles, so the x
+// it needs (16 MT rows of the unit) is read from LDS into registers once and
 // serves Tn tiles; split by columns instead, every wave would read all of x
-// and LDS bandwidth would bound the kernel from 32 rows on.  A last round of
-// up to four groups gives each group to two waves, 64 k each.
+// and LDS bandwidth would bound the kernel from 32 rows on.  A unit is a group
+// (128 k) up to 64 rows and half a group beyond, where the x of a whole one
+// would take 32 MT of a lane's registers.  With whole groups a last round of
+// up to four gives each to two waves, 64 k each.
 //
-// The waves share nothing before the end: a wave stages its group's x in LDS
+// The waves share nothing before the end: a wave stages its unit's x in LDS
 // of its own with direct-to-LDS loads (LDS only turns rows into operand
 // order), its weight blocks arrive in registers, and both are requested one
-// round ahead, right after the round's own have landed: no workgroup barrier
-// in the walk.
+// round ahead, as soon as the round's own x has gone from LDS to registers: no
+// workgroup barrier in the walk.
 //
 // Measured (graph replays over rotating weights, us a launch; before: the
 // staged kernel of 16 rows and fewer with up to four m-tiles, whose x chunk
 // fitted LDS only for K splits of 5 to 26): 2560 x 19456 at 32 / 48 / 64 rows
 // 12.5 / 14.6 / 16.7 (34 / 35 / 60 before, 17.4 / 17.6 / 18.1 as 64 x 128
 // blocks of the tiled kernel), 9728 x 2560 10.3 / 12.3 / 13.9 (21 / 22 / 37;
-// tiled 16.6 / 16.7 / 17.0).  Of the 16.7 us, 8.2 go to the loads (10.7 MB of
-// x per row of workgroups besides the weights), 3.3 to products that the loads
-// do not cover, 2.4 to the sums in LDS and 1.4 to the stores.  Requesting the
-// weights two rounds ahead (two copies of the walk's body) was 0.6 to 1.4 us
-// slower; a workgroup-wide pipeline of 4-group steps, two waves a group, with
-// a barrier a step took 15.3 us at 32 rows.
+// tiled 16.6 / 16.7 / 17.0).  Of the 16.7 us, 8.2 go to the loads (every
+// workgroup reads all of x, 327 KB, mostly from L2, beside its weights), 3.3
+// to products that the loads do not cover, 2.4 to the sums in LDS and 1.4 to
+// the stores.  Requesting the weights two rounds ahead (two copies of the
+// walk's body) was 0.6 to 1.4 us slower; a workgroup-wide pipeline of 4-group
+// steps, two waves a group, with a barrier a step took 15.3 us at 32 rows.
+// Beyond 64 rows, against the tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows
+// 10.9 / 12.8 / 15.4 (14.1 / 14.1 / 17.0), 2560 x 12288 at 65 / 90 rows
+// 13.3 / 15.4 (17.1 / 17.1), 512 x 2048 at 65 / 128 rows 4.3 / 5.2 (5.7 / 5.9).
 //
 // At the end the waves' sums are added in LDS in a fixed order: wave w + 4 to
 // wave w, then the four sums in order.
 //
 // x of a wave in LDS: 16-byte chunk c (k = 8 c) of row r at slot
-// 16 r + (c ^ (r & 15)), as in the tiled kernel: coalesced fills and operand
-// reads without bank conflicts.
-// Operand of s_waitcnt that waits until at most n vector-memory loads are in
-// flight, and for nothing else.
-constexpr int wait_vmcnt(int n) { return (n & 15) | (n >> 4) << 14 | 7 << 4 | 15 << 8; }
-
+// 16 r + (c ^ (r & 15)), as in the tiled kernel, or, with half-group units,
+// 8 r + (c ^ ((r >> 1) & 7)): coalesced fills and operand reads without bank
+// conflicts.
 template <int MT, int TN, bool SYM>
 __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
+    constexpr bool HG = MT > 4;                      // a wave's unit of K: half a group
+    constexpr int KJ = HG ? 2 : 4;                   // 32-wide steps of k in a unit
     constexpr int ROWS = 16 * MT, kHalf = kWaves / 2;
+    constexpr uint32_t kWaveX = ROWS * KJ * 64;      // LDS bytes of a wave's x
     constexpr int NS = (TN + 3) / 4;                 // scale loads per group: four tiles each
     constexpr int kSzBlk = kTileN * (SYM ? kSzBytesSym : kSzBytesAsym);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lm = lane & 15, lg = lane >> 4;
     const WgWork w = wg_work(a, blockIdx.x);
-    // rounds of this wave: whole ones, then its part of the last Kc % 8 groups
-    const int full = w.Kc / kWaves, rem = w.Kc % kWaves;
-    const bool paired = rem <= kHalf;
-    const int tail = paired ? wave >> 1 : wave;      // its group among the last ones
+    // work of this wave: rounds of 8 units, then its part of the last ones
+    const int units = HG ? 2 * w.Kc : w.Kc;
+    const int full = units / kWaves, rem = units % kWaves;
+    const bool paired = !HG && rem <= kHalf;
+    const int tail = paired ? wave >> 1 : wave;      // its unit among the last ones
     const int nr = full + (tail < rem ? 1 : 0);
+    auto unit_of = [&](int r) { return r < full ? r * kWaves + wave : full * kWaves + tail; };
+    auto group_of = [&](int u) { return HG ? u >> 1 : u; };
+    auto half_of = [&](int u) { return HG ? (uint32_t)(u & 1) : 0u; };
 
-    // x: load (mt, i) fills rows 16 mt + 4 i + (lane >> 4); rows >= M (only in
-    // the last m-tile) are copies of row M - 1 and feed no stored output
+    // x: load (mt, i) fills rows 16 mt + kRowsLoad i + lane / kChunks; rows >= M
+    // (only in the last m-tile) are copies of row M - 1 and feed no stored output
+    constexpr int kChunks = HG ? 8 : 16, kRowsLoad = 64 / kChunks, kLoads = 16 / kRowsLoad;
     const uint32_t row_bytes = (uint32_t)a.K * 2u;
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, (int)((uint32_t)a.M * row_bytes), kRsrcFlags);
-    uint32_t xv[4], xl[4];
+    auto swizzle = [&](int row, int c) { return HG ? c ^ ((row >> 1) & 7) : c ^ (row & 15); };
+    uint32_t xv[kLoads], xl[kLoads];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = 4 * i + lg;
-        xv[i] = (uint32_t)r * row_bytes + (uint32_t)(lm ^ r) * 16u;
-        xl[i] = (uint32_t)min(r, a.M - 1 - 16 * (MT - 1)) * row_bytes + (uint32_t)(lm ^ r) * 16u;
+    for (int i = 0; i < kLoads; ++i) {
+        const int r = kRowsLoad * i + lane / kChunks;
+        const uint32_t c = (uint32_t)swizzle(r, lane % kChunks) * 16u;
+        xv[i] = (uint32_t)r * row_bytes + c;
+        xl[i] = (uint32_t)min(r, a.M - 1 - 16 * (MT - 1)) * row_bytes + c;
     }
-    const uint32_t lds_x = lds_addr(smem) + wave * (ROWS * 256);
-    auto load_x = [&](int kb) {
+    const uint32_t lds_x = lds_addr(smem) + wave * kWaveX;
+    auto load_x = [&](int u) {
+        const uint32_t off = (uint32_t)(w.g0 + group_of(u)) * 256u + half_of(u) * 128u;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                load_lds_buf16(rx, mt == MT - 1 ? xl[i] : xv[i], (uint32_t)(w.g0 + kb) * 256u + mt * 16 * row_bytes,
-                               lds_x + (mt * 4 + i) * 1024u);
+            for (int i = 0; i < kLoads; ++i)
+                load_lds_buf16(rx, mt == MT - 1 ? xl[i] : xv[i], off + mt * 16 * row_bytes,
+                               lds_x + (mt * kLoads + i) * 1024u);
     };
     // weights and scales of group kb; lane (lg, lm) of scale load i holds column lm of tile 4 i + lg
     const size_t base = (size_t)w.t0 * a.Kb + w.g0;
@@ -91,36 +104,34 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         __builtin_amdgcn_make_buffer_rsrc((void *)(w.codes + base * 64), 0, span * 1024, kRsrcFlags);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const char *)w.sz + base * kSzBlk), 0, span * kSzBlk, kRsrcFlags);
-    const uint32_t cv = lane * 16;
     uint32_t sv[NS];
 #pragma unroll
     for (int i = 0; i < NS; ++i)
         sv[i] = (uint32_t)(min(4 * i + lg, w.Tn - 1) * a.Kb) * kSzBlk + sz_offset_bytes<SYM>(lm);
-    struct Group {
-        uint4 c[TN];
+    typedef uint32_t words_t __attribute__((ext_vector_type(KJ)));
+    struct Unit {
+        words_t c[TN];
         uint32_t s[NS];
     };
-    auto load_s = [&](Group &g, int i, int kb) {
-        g.s[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, sv[i], kb * kSzBlk, kWeightPolicy);
-    };
-    auto load_c = [&](Group &g, int t, int kb) {
-        g.c[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                               rc, cv, (min(t, w.Tn - 1) * a.Kb + kb) * 1024, kWeightPolicy));
-    };
-    auto load_w = [&](Group &g, int kb) {
+    auto load_w = [&](Unit &g, int u) {
+        const int kb = group_of(u);
 #pragma unroll
-        for (int i = 0; i < NS; ++i) load_s(g, i, kb);
+        for (int i = 0; i < NS; ++i) g.s[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, sv[i], kb * kSzBlk, kWeightPolicy);
 #pragma unroll
-        for (int t = 0; t < TN; ++t) load_c(g, t, kb);
+        for (int t = 0; t < TN; ++t) {
+            const uint32_t soff = (uint32_t)(min(t, w.Tn - 1) * a.Kb + kb) * 1024u;
+            if constexpr (HG)
+                g.c[t] = __builtin_amdgcn_raw_buffer_load_b64(rc, lane * 16 + half_of(u) * 8, soff, kWeightPolicy);
+            else
+                g.c[t] = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 16, soff, kWeightPolicy);
+        }
     };
-    auto group_of = [&](int r) { return r < full ? r * kWaves + wave : full * kWaves + tail; };
-
     v4f acc[TN][MT];
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[t][mt] = v4f{0, 0, 0, 0};
-    const uint4 *xb = (const uint4 *)smem + wave * (ROWS * 16) + lm * 16;
+    const uint4 *xb = (const uint4 *)(smem + wave * kWaveX) + lm * kChunks;
 
     // once per dequantization route (uniform in the workgroup: its tiles
     // belong to one member), the first loads included, so that none in flight
@@ -129,26 +140,22 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         constexpr bool F16 = decltype(route)::value;
         const ExtractConsts<F16> kx;
         const DeqSel<SYM, F16> dsel(lane);
-        // round r with its weights in g, which it refills for round r + 2.
-        // The loads of a round are issued in the order x (of the next
-        // round), weights (of the one after), so when only the weights of
-        // round r + 1 are left in flight, x and weights of round r are there.
-        // The wait is the builtin and not inline assembly: the compiler takes
-        // it into account and adds no waits of its own, which would count
-        // the x loads it does not see as older than they are.
-        auto round = [&](int r, Group &g) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            const Group cur = g;
-            v8bf xf[4][MT];
+        Unit g;
+        load_x(unit_of(0));
+        load_w(g, unit_of(0));
+        for (int r = 0; r < nr; ++r) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this round's x is in LDS
+            const Unit cur = g;
+            v8bf xf[KJ][MT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < KJ; ++j)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    xf[j][mt] = __builtin_bit_cast(v8bf, xb[mt * 256 + ((4 * j + lg) ^ lm)]);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // x is in registers: its LDS is free
+                    xf[j][mt] = __builtin_bit_cast(v8bf, xb[mt * 16 * kChunks + swizzle(lm, 4 * j + lg)]);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // and in registers: its LDS is free
             if (r + 1 < nr) {
-                load_x(group_of(r + 1));
-                load_w(g, group_of(r + 1));
+                load_x(unit_of(r + 1));
+                load_w(g, unit_of(r + 1));
             }
             uint32_t sz[4 * NS];
 #pragma unroll
@@ -161,33 +168,33 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
                 sz[4 * i + 2] = o[0];
                 sz[4 * i + 3] = o[1];
             }
-            // all 128 k of the group, or this wave's 64 of a shared last group
+            // all of the unit's k, or this wave's 64 of a shared last group
             const bool lo = r < full || !paired || (wave & 1) == 0, hi = r < full || !paired || (wave & 1) == 1;
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
-                if (t < w.Tn) {
-                    const MfmaDeq d = dsel.setup(sz[t]);
-                    auto word = [&](uint32_t P, int j) {
-                        const v8bf wa = mfma_dequant<F16>(P, d, kx);
+                if (t >= w.Tn) continue;
+                const MfmaDeq d = dsel.setup(sz[t]);
+                auto word = [&](int j) {
+                    const v8bf wa = mfma_dequant<F16>(cur.c[t][j], d, kx);
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt)
-                            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[j][mt], acc[t][mt], 0, 0, 0);
-                    };
+                    for (int mt = 0; mt < MT; ++mt)
+                        acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[j][mt], acc[t][mt], 0, 0, 0);
+                };
+                if constexpr (HG) {
+                    word(0);
+                    word(1);
+                } else {
                     if (lo) {
-                        word(cur.c[t].x, 0);
-                        word(cur.c[t].y, 1);
+                        word(0);
+                        word(1);
                     }
                     if (hi) {
-                        word(cur.c[t].z, 2);
-                        word(cur.c[t].w, 3);
+                        word(2);
+                        word(3);
                     }
                 }
             }
-        };
-        Group g;
-        load_x(group_of(0));
-        load_w(g, group_of(0));
-        for (int r = 0; r < nr; ++r) round(r, g);
+        }
     };
     if (nr > 0) {
         if (w.f16) walk(std::true_type{});
@@ -220,31 +227,22 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     write_sums<kHalf>(a, w, sums, TN, ROWS);
 }
 
+template <int MT, int TN, bool SYM>
+static FwdKernel pick_mid_tiles(int tn) {
+    if (tn == TN) return k_mid<MT, TN, SYM>;
+    if constexpr (TN > 1) return pick_mid_tiles<MT, TN - 1, SYM>(tn);
+    return nullptr;
+}
+
 template <int MT, bool SYM>
-static FwdKernel pick_mid_rows(int tn) {
-    switch (tn) {
-        case 1: return k_mid<MT, 1, SYM>;
-        case 2: return k_mid<MT, 2, SYM>;
-        case 3: return k_mid<MT, 3, SYM>;
-        case 4: return k_mid<MT, 4, SYM>;
-        case 5: return k_mid<MT, 5, SYM>;
-    }
-    if constexpr (mid_tiles_max(MT) >= 6)
-        if (tn == 6) return k_mid<MT, 6, SYM>;
-    if constexpr (mid_tiles_max(MT) >= 8) {
-        if (tn == 7) return k_mid<MT, 7, SYM>;
-        if (tn == 8) return k_mid<MT, 8, SYM>;
-    }
+static FwdKernel pick_mid_rows(int mrows, int tn) {
+    if (mrows == 16 * MT) return pick_mid_tiles<MT, mid_tiles_max(MT), SYM>(tn);
+    if constexpr (MT < kMidTilesM) return pick_mid_rows<MT + 1, SYM>(mrows, tn);
     return nullptr;
 }
 
 FwdKernel pick_mid(int mrows, int tn, bool symmetric) {
-    switch (mrows) {
-        case 32: return symmetric ? pick_mid_rows<2, true>(tn) : pick_mid_rows<2, false>(tn);
-        case 48: return symmetric ? pick_mid_rows<3, true>(tn) : pick_mid_rows<3, false>(tn);
-        case 64: return symmetric ? pick_mid_rows<4, true>(tn) : pick_mid_rows<4, false>(tn);
-    }
-    return nullptr;
+    return symmetric ? pick_mid_rows<2, true>(mrows, tn) : pick_mid_rows<2, false>(mrows, tn);
 }
 
 }  // namespace qlin

@@ -504,10 +504,11 @@ int make_tiled_plan(const Target &t, int64_t split_k, int64_t M, Plan *p) {
 }
 
 // Does the automatic choice run M rows through the TILED kernel (one
-// launch) rather than the decode kernels?  Above 64 rows, always: with its K
-// split the tiled kernel also covers the narrow, deep layers at small M
-// (measured on MI355X at M = 128: o projection 14.5 us against 35.9 us as two
-// 64-row launches, down projection 21.8 us against 74.2 us).
+// launch) rather than the decode kernels?  Above 64 rows, always (make_mid_plan
+// may still give the launch to k_mid): with its K split the tiled kernel also
+// covers the narrow, deep layers at small M (measured on MI355X at M = 128,
+// against two 64-row launches of k_mid: 4096 x 2560 13.4 us against 20.6,
+// 9728 x 2560 18.1 against 28.2).
 bool auto_tiled(int64_t M) { return M > kMaxSkinnyM; }
 
 // Decode-kernel plan (M <= 64) for the target.  The automatic choice (AUTO)
@@ -636,13 +637,52 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
     return QLIN_OK;
 }
 
-// The plan of a launch of M rows: TILED (forced, or AUTO above 64 rows) is
-// planned per member (one launch each); the decode kernels cover all members
+// k_mid beyond 64 rows (up to 144, without a K split), where it is estimated
+// faster than the tiled plan q the workspace allows.  Both estimates (us) are
+// fitted to 65 .. 144 rows of K = 512 .. 9728, N = 2048 .. 19456: per group of
+// K, k_mid pays for its m-tiles and tiles, the 64 x 128 blocks of the tiled
+// kernel 0.63 us (1.5 times that with two blocks a compute unit), the taller
+// ones 2 us, and a K split its partial blocks; of the 117 shapes timed there,
+// none came out more than 3 % slower than its tiled plan.  Measured, k_mid against the
+// tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows 10.9 / 12.8 / 15.4 us against
+// 14.1 / 14.1 / 17.0, 4096 x 6144 14.1 / 16.6 / 21.0 against 17.7 / 17.8 / 23.6;
+// at 112 rows both take 14.1 and past 144 rows x no longer fits LDS.
+bool make_mid_plan(const Target &t, int64_t M, const Plan &q, Plan *p) {
+    const int mt = (int)((M + 15) / 16);
+    if (mt > kMidTilesM) return false;
+    const int Gn = std::min(t.Nt, t.num_cu), Tn = ranges_tnmax(t, Gn);
+    if (Tn < 1 || Tn > mid_tiles_max(mt) || (int64_t)Tn * t.Kb * 1024 >= ((int64_t)1 << 31)) return false;
+    const double mid = 4.5 + t.Kb * (0.13 + 0.046 * mt + 0.024 * mt * (Tn - 2));
+    const int64_t blocks = (int64_t)q.Gn * ((M + q.mrows - 1) / q.mrows);
+    const double load = (double)((blocks * q.S + t.num_cu - 1) / t.num_cu);
+    const double group = q.tn == 2 ? 0.63 * (0.5 + 0.5 * load) : 2.0 * load;
+    double tiled = 4.0 + group * ((t.Kb + q.S - 1) / q.S);
+    if (q.S > 1) tiled += 1.0 + 2.0 * (double)q.floats * 4.0 / 4.0e6;
+    if (mid >= 0.97 * tiled) return false;
+    *p = Plan();
+    p->path = kTiled;
+    p->kern = kKernMid;
+    p->mrows = 16 * mt;
+    p->Gn = p->grid = Gn;
+    p->tn = p->TnMax = Tn;
+    split_ranges(t, Gn, Tn, p->gn);
+    p->lds = std::max(mid_lds_bytes(mt), (size_t)80 * 1024 + 256);
+    p->rows = (int)M;
+    return true;
+}
+
+// The plan of a launch of M rows: TILED (forced, or AUTO above 64 rows, where
+// k_mid may replace it) is one launch over all members; the decode kernels cover all members
 // in one launch per slice of p->rows rows.
 int make_plan(const Target &t, int path, int64_t split_k, int64_t M, Plan *p) {
     if (path < kAuto || path > kRegs) return fail(QLIN_ERR_INVALID, "unknown path %d", path);
     if (split_k < 0 || split_k > t.Kb) return fail(QLIN_ERR_INVALID, "split_k must be in [0, K/128]");
-    if (path == kTiled || (path == kAuto && auto_tiled(M))) return make_tiled_plan(t, split_k, M, p);
+    if (path == kTiled || (path == kAuto && auto_tiled(M))) {
+        const int rc = make_tiled_plan(t, split_k, M, p);
+        Plan mid;
+        if (rc == QLIN_OK && path == kAuto && split_k == 0 && p->rows == M && make_mid_plan(t, M, *p, &mid)) *p = mid;
+        return rc;
+    }
     return make_decode_plan(t, path, split_k, (int)std::min<int64_t>(M, kMaxSkinnyM), p);
 }
 
@@ -829,9 +869,9 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
 // caller.
 int launch_all(const Target &t, int path, int64_t split_k, int64_t M, const uint16_t *x, uint16_t *const *ys,
                void *ws, size_t ws_bytes, hipStream_t st) {
-    // rows left over by launches of a tiled plan stay with the tiled kernel
-    const int rest = path == kAuto && auto_tiled(M) ? kTiled : path;
     for (int64_t m0 = 0; m0 < M;) {
+        // rows left over by a launch of a tiled plan stay with the tiled kernel
+        const int rest = path == kAuto && auto_tiled(M) && m0 > 0 ? kTiled : path;
         Plan p;
         int rc = plan_for(t, rest, split_k, M - m0, &p);
         if (rc != QLIN_OK) return rc;
@@ -1054,8 +1094,10 @@ int plan_text(const Target &t, int path, int64_t split_k, int64_t M, char *buf, 
     const bool tiled = p.kern == kKernTiled;
     const int64_t launches = (M + p.rows - 1) / p.rows;
     static const char *names[] = {"gemv", "regs", "skinny", "tiled", "skinny"};
+    // k_mid serves rows of both paths: the plan names the one that chose it
+    const char *path_name = p.kern == kKernMid && p.path == kTiled ? "tiled" : names[p.kern];
     snprintf(buf, (size_t)buflen, "path=%s kernel=%s grid=%d block=%d split=%d ranges=%d lds=%zu launches=%lld",
-             names[p.kern], kernel_name(p.kern, p.mrows, p.tn, t.symmetric), p.grid,
+             path_name, kernel_name(p.kern, p.mrows, p.tn, t.symmetric), p.grid,
              tiled ? kTiledWaves * 64 * tiled_wsplit(TiledShape{p.mrows / 16, p.tn}) : kThreads, p.S, p.Gn, p.lds,
              (long long)launches);
     return QLIN_OK;

@@ -32,8 +32,8 @@ enum Path { kAuto = 0, kGemv = 1, kSkinny = 2, kTiled = 3, kRegs = 4 };
 enum Kern {
     kKernGemv = 0,     // k_gemv4: M <= 4, group-major walk, x in registers (GEMV path)
     kKernMfma16 = 1,   // k_mfma16: M <= 16, group-major walk, x in registers (REGS path)
-    kKernStaged = 2,   // k_skinny<MT>: M <= 64, tile-major walk, x chunk staged in LDS (SKINNY path)
-    kKernMid = 4,      // k_mid<MT, TN>: 17 <= M <= 64, K cut over the waves, whole groups each (SKINNY path)
+    kKernStaged = 2,   // k_skinny: M <= 16, tile-major walk, x chunk staged in LDS (SKINNY path)
+    kKernMid = 4,      // k_mid<MT, TN>: 17 <= M <= 144, K cut over the waves (SKINNY path, AUTO above 64 rows)
     kKernTiled = 3     // k_tiled: any M, 128 x 256 output blocks, x and weights staged in LDS (TILED path)
 };
 
@@ -130,12 +130,14 @@ inline size_t lds_bytes(int M, int Kc, int Tn) {
     return x + (size_t)kWaves * Tn * mrows * 16 * 4;
 }
 
-// k_mid (mid.hip) with mt m-tiles of 16 rows: most column tiles per workgroup
-// (4 mt accumulator registers each) and LDS bytes: 16 mt rows x 256 bytes of x
-// per wave (the four partial sums per tile that take their place need no more).
-constexpr int mid_tiles_max(int mt) { return mt == 2 ? 8 : mt == 3 ? 6 : 5; }
-constexpr size_t mid_lds_bytes(int mt) { return (size_t)kWaves * mt * 4096; }
-static_assert(4 * 8 * 1024 <= kWaves * 4096, "partial sums of 8 tiles fit where x was");
+// k_mid (mid.hip) with mt m-tiles of 16 rows, 2 .. kMidTilesM: most column
+// tiles per workgroup (4 mt accumulator registers each, beside the x of a unit
+// of K) and LDS bytes: the x of a wave's unit, a group up to 4 m-tiles and half
+// a group beyond (the four partial sums per tile that take its place need no more).
+constexpr int kMidTilesM = 9;
+constexpr int mid_tiles_max(int mt) { return mt == 2 ? 8 : mt == 3 ? 6 : mt == 4 ? 5 : mt < 7 ? 3 : 2; }
+constexpr size_t mid_lds_bytes(int mt) { return (size_t)kWaves * mt * (mt > 4 ? 2048 : 4096); }
+static_assert(4 * 8 * 1024 <= kWaves * 4096 && 4 * 3 * 1024 <= kWaves * 2048, "partial sums fit where x was");
 typedef void (*FwdKernel)(FwdArgs);
 FwdKernel pick_mid(int mrows, int tn, bool symmetric);
 

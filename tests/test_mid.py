@@ -1,4 +1,4 @@
-"""GPU tests of the 17 to 64 row kernel and of the two dequantization routes
+"""GPU tests of the 17 to 144 row kernel and of the two dequantization routes
 (needs an MI355X): the sizes where a workgroup's rounds, tiles and rows end
 unevenly, and the ends of the scale range that each route takes, against the
 oracle within max(2 bf16 ulp, 1e-3); integer sums and dequantized weights bit
@@ -33,6 +33,29 @@ def test_rounds_tiles_and_rows_end_unevenly(M, Kb, N):
         assert "kernel=k_mid" in lin.plan(M), lin.plan(M)
         assert_close(run(lin, c["x"], SKINNY), oracle(c, symmetric=sym), f"M={M} Kb={Kb} N={N} sym={sym}")
         lin.close()
+
+
+@pytest.mark.parametrize("M", [65, 80, 81, 96, 97, 112, 113, 128, 129, 144])
+@pytest.mark.parametrize("Kb,N", [(3, 48), (4, 16), (5, 208), (9, 224), (13, 4112)])
+def test_half_group_units_end_unevenly(M, Kb, N):
+    """Above 64 rows: half groups below, at and past the 8 of a round, one and
+    two tiles a workgroup, full and partial m-tiles; both formats."""
+    for sym in (False, True):
+        c = gen.random_case(M * 1000 + Kb * 10 + N + sym, M, 128 * Kb, N)
+        lin = make(c, symmetric=sym)
+        assert "path=tiled kernel=k_mid" in lin.plan(M), lin.plan(M)
+        assert_close(run(lin, c["x"]), oracle(c, symmetric=sym), f"M={M} Kb={Kb} N={N} sym={sym}")
+        lin.close()
+
+
+@pytest.mark.parametrize("M,N", [(65, 8208), (80, 12288), (81, 8208), (96, 12288)])
+def test_most_tiles_above_64_rows(M, N):
+    K = 128 * 20
+    c = gen.random_case(M + N, M, K, N)
+    lin = make(c)
+    assert "kernel=k_mid" in lin.plan(M), lin.plan(M)
+    assert_close(run(lin, c["x"]), oracle(c), f"M={M} N={N}")
+    lin.close()
 
 
 @pytest.mark.parametrize("M,split", [(17, 2), (33, 3), (64, 5)])
