@@ -51,7 +51,8 @@ extern "C" {
  *   nq         block queries, 1 <= nq <= 16
  *   T          cached tokens including the block, nq <= T <= 2^28
  *   window     W >= 0; 0 = full attention (no window)
- *   splits     0 = the planner's choice, else the number of key ranges per
+ *   splits     0 = the planner's choice (for few keys one range, one kernel
+ *              and no workspace), else the number of key ranges per
  *              key/value head (clamped to the number of 64-key tiles, at
  *              most 256)
  * Outputs (each may be NULL): *splits_out = the key ranges per key/value

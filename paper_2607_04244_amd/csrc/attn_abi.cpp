@@ -21,6 +21,7 @@ constexpr int64_t kMaxT = (int64_t)1 << 28;
 struct AttnPlan {
     int G = 1, half = -1, lo = 0, hi = 0, ntiles = 0, tps = 1, S = 1;
     int64_t ws_bytes = 0;
+    bool block = false;     // k_attn_block (S is 1)
 };
 
 int check_sizes(int64_t Hq, int64_t Hkv, int64_t D, int64_t nq, int64_t T, int64_t window, int64_t splits) {
@@ -36,7 +37,7 @@ int check_sizes(int64_t Hq, int64_t Hkv, int64_t D, int64_t nq, int64_t T, int64
 }
 
 // Key ranges per key/value head.  The automatic choice spreads the tiles
-// over about one workgroup per compute unit.
+// over about one workgroup per compute unit, or takes k_attn_block.
 int make_attn_plan(int64_t Hq, int64_t Hkv, int64_t nq, int64_t T, int64_t window, int64_t splits, AttnPlan *p) {
     p->G = (int)(Hq / Hkv);
     const bool full = window == 0 || T <= window;
@@ -50,7 +51,18 @@ int make_attn_plan(int64_t Hq, int64_t Hkv, int64_t nq, int64_t T, int64_t windo
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e != hipSuccess) return hip_fail(e, "device query");
-        S = std::max<int64_t>(1, cus / Hkv);
+        // Few keys: k_attn_block, whose workgroups each read all of a head's
+        // K, while it has a compute unit for each of them.  Measured in us,
+        // against the two kernels of the split: 32 / 8 heads at 64 / 160 / 272 /
+        // 320 / 384 keys 3.4 / 4.8 / 5.9 / 6.4 / 7.3 against 4.4 / 7.1 / 7.3 /
+        // 7.3 / 7.4, 8 / 8 heads at 320 / 352 keys 6.4 / 6.8 against 6.5 / 6.5,
+        // 64 / 8 heads (two heads a wave of the split) at 384 keys 7.3 against
+        // 9.7; 512 / 64 heads at 160 keys, two workgroups a compute unit and
+        // more, 19.4 against 16.5.
+        const int keys = p->hi - p->lo;
+        p->block = keys <= (p->G > kAttnWaves ? kAttnBlockUnits : kAttnBlockUnits - 2) * kAttnUnit &&
+                   Hq * (kAttnD / kAttnSlice) <= cus;
+        S = p->block ? 1 : std::max<int64_t>(1, cus / Hkv);
     }
     S = std::min<int64_t>({S, (int64_t)p->ntiles, (int64_t)kAttnMaxSplits});
     p->tps = (int)((p->ntiles + S - 1) / S);
@@ -79,7 +91,8 @@ int qlin_swa_plan(int64_t Hq, int64_t Hkv, int64_t head_dim, int64_t nq, int64_t
     if (workspace_bytes) *workspace_bytes = p.ws_bytes;
     if (buf && buflen > 0)
         snprintf(buf, (size_t)buflen, "kernel=%s keys=%d tiles=%d splits=%d grid=%lld combine=%d",
-                 attn_kernel_name(p.G), p.hi - p.lo, p.ntiles, p.S, (long long)(Hkv * p.S), p.S > 1 ? 1 : 0);
+                 attn_kernel_name(p.G, p.block), p.hi - p.lo, p.ntiles, p.S, (long long)(p.block ? Hq * (kAttnD / kAttnSlice) : Hkv * p.S),
+                 p.S > 1 ? 1 : 0);
     return QLIN_OK;
 }
 
@@ -124,7 +137,7 @@ int qlin_swa_attention(int64_t Hq, int64_t Hkv, int64_t head_dim, int64_t nq, in
     a.tps = p.tps;
     a.S = p.S;
     a.c = (float)(1.4426950408889634 / std::sqrt((double)kAttnD));
-    hipError_t e = launch_attn(a, (hipStream_t)stream);
+    const hipError_t e = p.block ? launch_attn_block(a, (hipStream_t)stream) : launch_attn(a, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "attention launch");
     return QLIN_OK;
 }

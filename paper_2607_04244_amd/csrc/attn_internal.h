@@ -18,6 +18,9 @@ namespace qlin {
 constexpr int kAttnD = 128;        // head dimension
 constexpr int kAttnQ = 16;         // block queries (one MFMA tile of rows)
 constexpr int kAttnTile = 64;      // keys per pipeline step
+constexpr int kAttnUnit = 32;      // k_attn_block: keys of a wave,
+constexpr int kAttnBlockUnits = 12;   // most waves of a workgroup
+constexpr int kAttnSlice = 32;     // and its output dimensions
 constexpr int kAttnWaves = 4;      // one query head per wave (two when G > 4)
 constexpr int kAttnMaxG = 8;       // query heads per key/value head
 constexpr int kAttnMaxSplits = 256;
@@ -37,6 +40,7 @@ struct AttnArgs {
 };
 
 hipError_t launch_attn(const AttnArgs &a, hipStream_t st);
-const char *attn_kernel_name(int G);
+hipError_t launch_attn_block(const AttnArgs &a, hipStream_t st);   // k_attn_block: no workspace
+const char *attn_kernel_name(int G, bool block);
 
 }  // namespace qlin
