@@ -49,7 +49,7 @@ enum {
 enum {
     QLIN_PATH_AUTO = 0,
     QLIN_PATH_GEMV = 1,    /* vector-ALU dequantize + v_dot2 dot product, M <= 4 */
-    QLIN_PATH_SKINNY = 2,  /* matrix-core dequantize + MFMA 16x16x32, x chunk staged in LDS, M <= 64 */
+    QLIN_PATH_SKINNY = 2,  /* matrix-core dequantize + MFMA 16x16x32, x staged in LDS, M <= 64 */
     QLIN_PATH_TILED = 3,   /* LDS-tiled MFMA GEMM for prefill-sized M */
     QLIN_PATH_REGS = 4     /* matrix-core dequantize + MFMA 16x16x32, x fragments in registers, M <= 16 */
 };
@@ -157,8 +157,8 @@ int qlin_plan(qlin_t h, int path, int64_t split_k, int64_t M, char *buf, int64_t
  * that share the input x: one launch of the decode kernels covers all of
  * them (M <= 64), e.g. the q, k and v projections of a decoder layer, which
  * the target runs on every verification step (Sec. 2.2) and the drafter on
- * every drafting step (Sec. 2.3).  For M > 64 (or path TILED) one tiled
- * launch covers all members as well.  n = 1 is a forward of one handle with
+ * every drafting step (Sec. 2.3).  For M > 64 (or path TILED) one launch of
+ * the prefill kernels covers all members as well.  n = 1 is a forward of one handle with
  * a caller workspace.
  *
  *   n          1 <= n <= 8 handles, all with the same K, the same format

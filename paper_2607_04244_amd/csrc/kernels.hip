@@ -26,7 +26,9 @@
 //     D = A . diag(s) + C,  A[k][r] = 128 + q[n_r][k],  C = -(128 + z) s,
 // i.e. D[k][n] = (q - z) * s exactly (each product has <= 16 significant
 // bits, the sum is exactly representable).  v_cvt_pk_bf16_f32 then rounds
-// each value once, to nearest even.  The vector-ALU route does the same with
+// each value once, to nearest even.  Handles whose scales allow it take the
+// codes as f16 subnormals instead, with the same products scaled by a power of
+// two (device_common.h).  The vector-ALU route does the bf16 form with
 // v_dot2_f32_bf16 on the same extracted pairs.  Both routes are bit-identical
 // to the definition; the unpack/dequantize test hooks check that.
 
