@@ -6,9 +6,9 @@
 //
 // A short key range runs in one kernel, k_attn_block; otherwise two kernels,
 // flash-decoding style:
-//   k_attn_split<HPW>  workgroup (key/value head h, split s): the G query
-//       heads of h (one per wave; two per wave when G > 4) against the 64-key
-//       tiles of split s.  Q, K and V arrive through direct-to-LDS loads, up
+//   k_attn_split       workgroup (key/value head h, split s): the G query
+//       heads of h (one per wave; for G > 4 two per wave, or half of the heads
+//       in a second workgroup) against the 64-key tiles of split s.  Q, K and V arrive through direct-to-LDS loads, up
 //       to three tiles ahead; K sits in XOR-swizzled 16-byte units (the MFMA
 //       A-operand reads are free of bank conflicts) and each V tile is
 //       transposed once, LDS to LDS, into key-contiguous rows (the A operand
@@ -88,7 +88,9 @@ __device__ inline int tile_unit(int kk, int c) { return kk * 16 + (c ^ (kk & 15)
 // Wave w takes query head w % 4 (and w % 4 + 4 when G > 4) and keys
 // 32 (w / 4) .. + 31 of every tile; the two halves of a head are merged
 // through LDS at the end.
-template <int HPW, int NS>
+// NG workgroups share the query heads of a (head, split); a template argument,
+// since computing the share cost the common case 0.2 us of its 15.
+template <int HPW, int NS, int NG>
 __global__ __launch_bounds__(kSplitWaves * 64, 1) void k_attn_split(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) uint4 qs[HPW * kAttnWaves * kQUnits];
     __shared__ __attribute__((aligned(16))) uint4 ring[2][NS][kTileUnits];   // K tiles, V tiles
@@ -101,15 +103,18 @@ __global__ __launch_bounds__(kSplitWaves * 64, 1) void k_attn_split(AttnArgs a) 
     // XCD-aware placement (workgroup b runs on XCD b % 8): with a multiple of
     // 8 key/value heads, every split of head h runs on XCD h % 8, so the
     // head's queries are fetched from HBM once and its partials stay in one L2
-    int h, s;
+    const int per = a.S * NG;
+    int h, rest;
     if ((a.Hkv & 7) == 0) {
-        const int q8 = blockIdx.x >> 3, hb = q8 / a.S;
+        const int q8 = blockIdx.x >> 3, hb = q8 / per;
         h = (blockIdx.x & 7) + 8 * hb;
-        s = q8 - hb * a.S;
+        rest = q8 - hb * per;
     } else {
-        h = blockIdx.x / a.S;
-        s = blockIdx.x - h * a.S;
+        h = blockIdx.x / per;
+        rest = blockIdx.x - h * per;
     }
+    const int s = rest / NG;
+    const int gs = (a.G + NG - 1) / NG, g0 = NG == 1 ? 0 : (rest - s * NG) * gs;   // its query heads: [g0, g0 + gs)
     const int t0 = s * a.tps, t1 = min(t0 + a.tps, a.ntiles);
     const uint16_t *kh = a.k + (size_t)h * a.kv_stride;
     const uint16_t *vh = a.v + (size_t)h * a.kv_stride;
@@ -119,8 +124,8 @@ __global__ __launch_bounds__(kSplitWaves * 64, 1) void k_attn_split(AttnArgs a) 
 #pragma unroll
     for (int hh = 0; hh < HPW; ++hh) {
         const int gl = hw + kAttnWaves * hh;
-        has[hh] = gl < a.G;
-        hq[hh] = h * a.G + (has[hh] ? gl : 0);
+        has[hh] = NG == 1 ? gl < a.G : gl < gs && g0 + gl < a.G;
+        hq[hh] = h * a.G + (has[hh] ? g0 + gl : 0);
     }
 
     // block queries (rows >= nq repeat row nq - 1; their results are discarded)
@@ -529,8 +534,8 @@ __global__ __launch_bounds__(kCombWaves * 64) void k_attn_combine(AttnArgs a) {
 
 }  // namespace
 
-const char *attn_kernel_name(int G, bool block) {
-    return block ? "k_attn_block" : G > kAttnWaves ? "k_attn_split<2,3>" : "k_attn_split<1,4>";
+const char *attn_kernel_name(int G, int ng, bool block) {
+    return block ? "k_attn_block" : G > kAttnWaves * ng ? "k_attn_split<2,3>" : "k_attn_split<1,4>";
 }
 
 hipError_t launch_attn_block(const AttnArgs &a, hipStream_t st) {
@@ -540,12 +545,13 @@ hipError_t launch_attn_block(const AttnArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_attn(const AttnArgs &a, hipStream_t st) {
+hipError_t launch_attn(const AttnArgs &a, int ng, hipStream_t st) {
     const dim3 block(kSplitWaves * 64);
-    const dim3 grid((unsigned)(a.Hkv * a.S));
+    const dim3 grid((unsigned)(a.Hkv * a.S * ng));
     // one head per wave: four tiles in flight (144 KiB of LDS); two heads: three (128 KiB)
-    if (a.G > kAttnWaves) hipLaunchKernelGGL((k_attn_split<2, 3>), grid, block, 0, st, a);
-    else hipLaunchKernelGGL((k_attn_split<1, 4>), grid, block, 0, st, a);
+    if (ng == 2) hipLaunchKernelGGL((k_attn_split<1, 4, 2>), grid, block, 0, st, a);
+    else if (a.G > kAttnWaves) hipLaunchKernelGGL((k_attn_split<2, 3, 1>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_attn_split<1, 4, 1>), grid, block, 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.S == 1) return e;
     hipLaunchKernelGGL(k_attn_combine, dim3((unsigned)(a.Hq * 8)), dim3(kCombWaves * 64), 0, st, a);

@@ -39,8 +39,8 @@ struct AttnArgs {
     float c;                // log2(e) / sqrt(128): scores to base-2 exponents
 };
 
-hipError_t launch_attn(const AttnArgs &a, hipStream_t st);
+hipError_t launch_attn(const AttnArgs &a, int ng, hipStream_t st);   // ng (1 or 2) workgroups share a head's queries
 hipError_t launch_attn_block(const AttnArgs &a, hipStream_t st);   // k_attn_block: no workspace
-const char *attn_kernel_name(int G, bool block);
+const char *attn_kernel_name(int G, int ng, bool block);
 
 }  // namespace qlin

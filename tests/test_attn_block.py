@@ -1,6 +1,7 @@
 """GPU tests of the drafter attention's one-kernel route for short key ranges
-(needs an MI355X), against the float64 oracle within the tolerance derived in
-test_attn: the edges of its 32-key units and of the rule that chooses it.
+and of the split whose workgroups share a key/value head's query heads (needs
+an MI355X), against the float64 oracle within the tolerance derived in
+test_attn: the edges of the 32-key units and of the rules.
 """
 
 import pytest
@@ -30,6 +31,22 @@ def test_rule_edges(Hq, Hkv, T, block):
     assert ("k_attn_block" in text) == block, text
     q, k, v = case(Hq, Hkv, 16, T, seed=T)
     check(q, k, v, T, 0, what=f"{Hq}/{Hkv} T={T}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,nq,T,W", [(5, 1, 16, 700, 0), (12, 2, 9, 2000, 1024), (21, 3, 16, 1000, 0),
+                                           (64, 8, 16, 1300, 0), (128, 16, 16, 500, 0), (40, 8, 1, 385, 0)])
+def test_two_workgroups_share_a_heads_queries(Hq, Hkv, nq, T, W):
+    S, ws, text = qlin.qlin_swa_plan(Hq, Hkv, 128, nq, T, W)
+    assert "k_attn_split<1,4>" in text and f"grid={2 * Hkv * S} " in text, text
+    q, k, v = case(Hq, Hkv, nq, T, seed=Hq + T)
+    check(q, k, v, T, W, what=f"{Hq}/{Hkv} nq={nq} T={T} W={W}")
+
+
+def test_too_many_heads_to_share_keep_two_heads_a_wave():
+    text = qlin.qlin_swa_plan(160 * 5, 160, 128, 16, 400, 0)[2]
+    assert "k_attn_split<2,3>" in text, text
+    q, k, v = case(160 * 5, 160, 4, 400, seed=3)
+    check(q, k, v, 400, 0, what="160 key/value heads")
 
 
 def test_forced_single_split_keeps_its_kernel():
