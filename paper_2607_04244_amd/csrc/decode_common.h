@@ -24,10 +24,7 @@ struct WgWork {
 // then the member's fields in one more.
 __device__ inline WgWork wg_work(const FwdArgs &a, int bid) {
     WgWork w;
-    // bid / Gn as a multiply-high by ceil(2^32 / Gn): exact because bid * Gn
-    // stays below 2^32 (bid < 64 * 4096 workgroups, Gn <= 4096); for Gn = 1
-    // the reciprocal is 0 and the chunk is bid itself
-    w.c = (int)(__umulhi((uint32_t)bid, a.inv_gn) + (a.Gn == 1 ? (uint32_t)bid : 0u));
+    w.c = gn_chunk(bid, a.Gn, a.inv_gn, a.gn_shift);
     w.jn = bid - w.c * a.Gn;
     int m = 0, g0 = 0;                        // the member owning range jn, its first range
 #pragma unroll

@@ -759,7 +759,7 @@ FwdArgs fwd_args(const Target &t, const Plan &p, int64_t M, const uint16_t *x, u
     a.Kb = t.Kb;
     a.S = p.S;
     a.Gn = p.Gn;
-    a.inv_gn = p.Gn > 1 ? (uint32_t)((((uint64_t)1 << 32) + p.Gn - 1) / p.Gn) : 0u;
+    gn_reciprocal(p.Gn, &a.inv_gn, &a.gn_shift);
     a.Kq = t.Kb / p.S;
     a.Kr = t.Kb % p.S;
     a.TnMax = p.TnMax;

@@ -58,7 +58,8 @@ struct FwdArgs {
     float *ws;              // fp32 partial sums (S > 1): S * Gn regions of TnMax * M * 16
     uint32_t *counters;     // [Gn] arrival counters (S > 1), zero between launches
     int M, K, Kb, S, Gn;
-    uint32_t inv_gn;        // ceil(2^32 / Gn) (0 for Gn = 1): chunk of workgroup b = umulhi(b, inv_gn)
+    uint32_t inv_gn;        // chunk of workgroup b: gn_chunk(b, Gn, inv_gn, gn_shift)
+    int gn_shift;
     int Kq, Kr;
     int TnMax;              // tiles of the widest column range
     uint32_t ws_bytes;      // size of ws (bounds of its buffer descriptor)
@@ -67,6 +68,23 @@ struct FwdArgs {
     FwdMember mem[kMaxMembers];
 };
 static_assert((kWaves & (kWaves - 1)) == 0, "waves per workgroup must be a power of two");
+
+// b / Gn without a division, for every workgroup index b < 2^31 and any Gn: with
+// 2^s < Gn <= 2^(s + 1) and inv = ceil(2^(32 + s) / Gn) < 2^32, inv Gn exceeds
+// 2^(32 + s) by d < Gn <= 2^(s + 1), so b d < 2^(32 + s) and the quotient
+// b inv / 2^(32 + s) never reaches the next whole number.  (Without the shift it
+// is exact only while b Gn < 2^32: a launch without a K split has as many ranges
+// as its columns need, over 100000 for eight members of the widest layer.)
+// Gn = 1 is the one value without such an s: inv is 0 there.
+inline void gn_reciprocal(int Gn, uint32_t *inv, int *shift) {
+    int s = 0;
+    while (((int64_t)2 << s) < Gn) ++s;
+    *shift = s;
+    *inv = Gn > 1 ? (uint32_t)((((uint64_t)1 << (32 + s)) + Gn - 1) / Gn) : 0u;
+}
+__host__ __device__ inline int gn_chunk(int b, int Gn, uint32_t inv, int shift) {
+    return (int)((uint32_t)(((uint64_t)(uint32_t)b * inv) >> 32) >> shift) + (Gn == 1 ? b : 0);
+}
 
 // TILED kernel (prefill-sized M): a workgroup of kTiledWaves x WS waves
 // computes a (16 MSW) x (64 NT) block of y; wave w owns all 16 MSW rows of

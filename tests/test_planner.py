@@ -1,0 +1,75 @@
+"""The launch planner on the CPU: plan_check.cpp compiles csrc/qlin.cpp for the
+host, without kernels, and plans groups of layers of any size on a device of
+256 compute units.
+"""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2607_04244_amd import qlin
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+AUTO, GEMV, SKINNY, TILED, REGS = qlin.PATH_AUTO, qlin.PATH_GEMV, qlin.PATH_SKINNY, qlin.PATH_TILED, qlin.PATH_REGS
+
+
+class Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int64) for n in ("kern", "S", "Gn", "TnMax", "rows", "ws_bytes")]
+
+
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    if shutil.which("g++") is None or not os.path.exists(os.path.join(ROCM, "include", "hip", "hip_runtime.h")):
+        pytest.skip("needs g++ and the HIP headers")
+    so = str(tmp_path_factory.mktemp("plan") / "plan_check.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-I",
+                    os.path.join(ROCM, "include"), "-o", so, os.path.join(HERE, "plan_check.cpp"),
+                    "-L", os.path.join(ROCM, "lib"), "-lamdhip64", "-Wl,-rpath," + os.path.join(ROCM, "lib")],
+                   check=True)
+    lib = ctypes.CDLL(so)
+    i64 = ctypes.c_int64
+    members = [ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+    lib.pc_plan.argtypes = members + [ctypes.c_int, ctypes.c_int, i64, i64, i64, ctypes.POINTER(Plan)]
+    lib.pc_wrong_work.argtypes = members + [ctypes.c_int, i64, i64, i64]
+    lib.pc_wrong_work.restype = i64
+    lib.pc_wrong_chunks.argtypes = [ctypes.c_int, i64]
+    lib.pc_wrong_chunks.restype = i64
+    return lib
+
+
+def _members(Ns, K):
+    return len(Ns), (ctypes.c_int * len(Ns))(*Ns), K
+
+
+def plan(lib, Ns, K, M, path=AUTO, split=0, ws=-1, symmetric=False):
+    """(status, Plan) of one launch over linears of K x N for each N."""
+    p = Plan()
+    rc = lib.pc_plan(*_members(Ns, K), symmetric, path, split, M, ws, ctypes.byref(p))
+    return rc, p
+
+
+@pytest.mark.parametrize("Ns,K,M,path,split", [
+    ([1 << 20] * 8, 128, 64, AUTO, 0),         # over 100000 ranges, no K split
+    ([1048512] * 8, 128, 48, AUTO, 0),
+    ([1 << 20], 128, 64, SKINNY, 0),
+    ([1 << 20] * 8, 256, 16, AUTO, 0),
+    ([1 << 20] * 8, 128, 16, REGS, 0),
+    ([1 << 20] * 8, 128, 4, GEMV, 0),
+    ([8 * 16 * 4095], 65536, 4, REGS, 512),    # the most chunks over the most ranges
+    ([256], 65536, 16, REGS, 64),
+    ([16], 1024, 3, GEMV, 8),                  # one range
+])
+def test_every_workgroup_finds_its_chunk(planner, Ns, K, M, path, split):
+    """A workgroup's chunk and range are bid / Gn and bid % Gn for every launch
+    the planner accepts; a quotient one too large makes it read and write
+    outside its member."""
+    assert planner.pc_wrong_work(*_members(Ns, K), path, split, M, -1) == 0
+
+
+def test_chunk_of_any_range_count(planner):
+    for Gn in list(range(1, 300)) + [2 ** i + d for i in range(9, 22) for d in (-1, 0, 1)] + [4093, 87376, 104864, 524287]:
+        assert planner.pc_wrong_chunks(Gn, min(512, (2 ** 31 - 1) // Gn)) == 0, Gn
