@@ -606,18 +606,6 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         if (split_k > 0) return fail(QLIN_ERR_UNSUPPORTED, "split_k=%d does not fit (LDS or workspace)", (int)split_k);
         return fail(QLIN_ERR_UNSUPPORTED, "no work split fits this shape and workspace");
     }
-    // Past 48 rows with every workgroup at k_mid's tile limit, a caller's
-    // workspace that holds three chunks takes the tiled kernel's K split: not
-    // for speed (2560 x 19456 at 64 rows 20.8 us against 16.6 in k_mid), but
-    // because such a launch has always reported and used one
-    if (auto_pick && bestK == kKernMid && bestS == 1 && Mi > 48 && bestTn == mid_tiles_max(4) && t.Kb >= 3) {
-        Plan q;
-        if (make_tiled_plan(t, 3, Mi, &q) == QLIN_OK) {
-            *p = q;
-            return QLIN_OK;
-        }
-        clear_err();
-    }
     p->kern = bestK;
     p->mrows = rows_of(bestK);
     p->S = bestS;
@@ -1038,7 +1026,7 @@ int run_forward(qlin_s *h, int path, int64_t split_k, int64_t M, const uint16_t 
     if (path == kGemv && M > kMaxGemvM) return fail(QLIN_ERR_UNSUPPORTED, "GEMV path needs M <= %d", kMaxGemvM);
     const hipStream_t st = (hipStream_t)stream;
     const CachedPlan *cp = (path == kAuto && split_k == 0 && M <= kMaxSkinnyM) ? &h->auto_plans[M - 1] : nullptr;
-    if (cp && cp->ok && cp->p.rows >= M && cp->p.kern != kKernTiled) {     // the automatic plan, computed at creation: one launch
+    if (cp && cp->ok && cp->p.rows >= M) {     // the automatic plan, computed at creation: one launch
         const FwdArgs a = fwd_args(t, cp->p, M, x, ys, h->ws, h->ws_bytes, 0);
         const hipError_t e = launch_forward(cp->p.kern, cp->p.mrows, cp->p.tn, t.symmetric, cp->p.grid, cp->p.lds, a, st);
         if (e != hipSuccess) return hip_fail(e, "forward launch");

@@ -168,9 +168,10 @@ def test_one_workspace_shared_in_stream_order():
 
 def test_small_workspace_gives_a_plan_that_fits():
     """A workspace smaller than the unconstrained plan's: the planner falls back
-    to a plan that fits it (16-row slices or no K split), with the same
-    results; a forced split that does not fit is refused."""
-    c = gen.random_case(70, 64, 2560, 19456)
+    to a plan that fits it (fewer K chunks or none), with the same results; a
+    forced split that does not fit is refused.  The deep, narrow layer is one
+    whose fastest plan at 64 rows cuts the K range."""
+    c = gen.random_case(70, 64, 9728, 2560)
     lin = make(c)
     need, plan = qlin.group_plan([lin], 64)
     assert need > 0, plan
@@ -181,7 +182,7 @@ def test_small_workspace_gives_a_plan_that_fits():
         assert ref.compare(group_run([lin], c["x"], ws_bytes=nb)[0], y_ref)["ok"], nb
     x = dev(c["x"])
     with pytest.raises(qlin.QlinError) as e:
-        qlin.forward_group([lin], x, path=SKINNY, split_k=3, workspace=None)
+        qlin.forward_group([lin], x, path=SKINNY, split_k=9, workspace=None)
     assert e.value.code == qlin.QLIN_ERR_UNSUPPORTED
     lin.close()
 

@@ -73,3 +73,14 @@ def test_every_workgroup_finds_its_chunk(planner, Ns, K, M, path, split):
 def test_chunk_of_any_range_count(planner):
     for Gn in list(range(1, 300)) + [2 ** i + d for i in range(9, 22) for d in (-1, 0, 1)] + [4093, 87376, 104864, 524287]:
         assert planner.pc_wrong_chunks(Gn, min(512, (2 ** 31 - 1) // Gn)) == 0, Gn
+
+
+@pytest.mark.parametrize("Ns,K,M,split", [([32768], 512, 64, 0), ([24576], 512, 50, 0), ([32768], 384, 64, 0),
+                                          ([19456], 2560, 64, 0), ([26464, 400], 512, 62, 0), ([151936], 2560, 64, 0),
+                                          ([20480], 896, 49, 1)])
+def test_wide_layers_at_49_to_64_rows_need_no_scratch(planner, Ns, K, M, split):
+    """One launch without a K split, whatever workspace there is: the launch
+    without an allocation, whose scratch is 16 MiB, takes them all."""
+    for ws in (-1, 0, 16 << 20):
+        rc, p = plan(planner, Ns, K, M, split=split, ws=ws)
+        assert rc == qlin.QLIN_OK and (p.S, p.ws_bytes, p.rows) == (1, 0, M), (ws, rc, p.S, p.ws_bytes, p.rows)

@@ -72,6 +72,24 @@ def test_grouped_launch_two_calls():
         l.close()
 
 
+@pytest.mark.parametrize("M,K,N", [(49, 384, 32768), (50, 512, 24576), (64, 512, 32768)])
+def test_wide_shallow_layers_at_49_to_64_rows(M, K, N):
+    """More columns than one round of workgroups holds, without a K split: no
+    scratch is needed, so the call is accepted."""
+    c = gen.random_case(K + N + M, M, K, N)
+    lin = qlin.QLinear(c["packed"], c["scales"], c["zeros"])
+    assert qlin.group_plan([lin], M)[0] == 0
+    x = dev(c["x"])
+    y = torch.full((M, N), 3.0, dtype=torch.bfloat16, device="cuda")
+    rc = qlin.qlin_forward_group_noalloc([lin.h], AUTO, 0, M, x.data_ptr(), [y.data_ptr()],
+                                         torch.cuda.current_stream().cuda_stream)
+    assert rc == qlin.QLIN_OK, qlin.last_error()
+    torch.cuda.synchronize()
+    r = ref.compare(host_bits(y), ref.forward(c["x"], c["packed"], c["scales"], c["zeros"]))
+    assert r["ok"], r
+    lin.close()
+
+
 def test_plans_beyond_the_static_scratch_are_refused():
     """A forced split whose partial sums exceed the 16 MiB array is refused
     before any launch, with the size in the message."""
