@@ -192,7 +192,7 @@ struct Plan {
     size_t lds = 0;
     int TnMax = 1;     // tiles of the widest column range
     int gn[kMaxMembers] = {};   // column ranges of each member
-    int rows = 0;      // rows per launch (decode kernels: M, or 16-row slices)
+    int rows = 0;      // rows per launch (fewer than M: see make_tiled_plan and make_decode_plan)
     size_t floats = 0; // fp32 partial sums the plan writes (K split)
     int counters = 0;  // arrival counters it uses (K split)
 };
@@ -513,9 +513,7 @@ bool auto_tiled(int64_t M) { return M > kMaxSkinnyM; }
 
 // Decode-kernel plan (M <= 64) for the target.  The automatic choice (AUTO)
 // searches the kernel families and K splits that fit LDS and the workspace;
-// 17 .. 64 rows run as k_mid, which needs neither a split nor a workspace.  When
-// nothing fits it runs 16-row slices, whose plans never need more than a
-// register-kernel launch without a split.
+// 17 .. 64 rows run as k_mid, which needs neither a split nor a workspace.
 int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p) {
     const bool auto_pick = path == kAuto;
     if (path == kAuto) path = (Mi <= gemv_max_auto()) ? kGemv : kSkinny;
@@ -545,12 +543,7 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         const int Kc = (t.Kb + S - 1) / S;
         if (S > 1 && ((size_t)S * Gn * Tn * Mi * 16 > t.cap_floats || Gn > t.cap_counters)) return -1;
         if (Tn > tn_max_of(kern)) return -1;
-        if (kern == kKernMid) {
-            // a forced split keeps the limit it is documented with: its chunk
-            // of x must fit LDS (the automatic plans have no such limit)
-            if (split_k > 0 && !chunk_fits(Mi, Kc)) return -1;
-            return (int64_t)Tn * t.Kb * 1024 < ((int64_t)1 << 31) ? Tn : -1;   // span of its descriptors
-        }
+        if (kern == kKernMid) return (int64_t)Tn * t.Kb * 1024 < ((int64_t)1 << 31) ? Tn : -1;   // span of its descriptors
         if (kern != kKernStaged) return lds_bytes_regs(rows_of(kern), Tn) <= kLdsMax ? Tn : -1;
         if (!chunk_fits(Mi, Kc)) return -1;
         if ((int64_t)Tn * Kc >= 65536) return -1;   // the kernel's block walk divides u < 2^16 by Kc
@@ -574,6 +567,11 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         while (Gn < t.Nt && fits(kern, S, Gn) < 0) ++Gn;
         return Gn;
     };
+    // A forced split at 17 .. 64 rows is taken where its chunk of x and its
+    // partial sums fit LDS, the limit it has always had: k_mid could run more,
+    // but what is refused does not depend on the kernel behind a path.
+    const bool forced_fits = split_k == 0 || Mi <= 16 || path == kGemv || path == kRegs ||
+                             fits(kKernStaged, (int)split_k, gn_for(kKernStaged, (int)split_k)) > 0;
 
     int bestK = -1, bestS = -1, bestGn = 1, bestTn = 1;
     // a measured plan for this shape, if it fits; otherwise the cost model
@@ -586,7 +584,7 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         }
     }
     double best = 1e300;
-    for (int ki = 0; ki < nk && !tuned; ++ki) {
+    for (int ki = 0; ki < nk && !tuned && forced_fits; ++ki) {
         const int kern = kerns[ki];
         const int s_lo = split_k > 0 ? (int)split_k : 1;
         const int s_hi = split_k > 0 ? (int)split_k : std::min(t.Kb, 64);
@@ -599,10 +597,12 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
         }
     }
     if (bestS < 0) {
-        // nothing fits the workspace at this M: 16-row slices (the automatic
-        // choice, or the staged kernel with the planner's split)
-        if ((auto_pick || (path == kSkinny && split_k == 0)) && Mi > 16)
-            return make_decode_plan(t, auto_pick ? kAuto : kSkinny, 0, 16, p);
+        // forced splits only (an unsplit k_mid fits any shape and workspace).
+        // More ranges than arrival counters at k_mid's tile limit: slices of 16
+        // rows, whose kernel takes wider ranges; a split that does not fit is
+        // dropped by the automatic choice and refused on a forced path
+        if (Mi > 16 && forced_fits) return make_decode_plan(t, auto_pick ? kAuto : kSkinny, split_k, 16, p);
+        if (Mi > 16 && auto_pick) return make_decode_plan(t, kAuto, 0, Mi, p);
         if (split_k > 0) return fail(QLIN_ERR_UNSUPPORTED, "split_k=%d does not fit (LDS or workspace)", (int)split_k);
         return fail(QLIN_ERR_UNSUPPORTED, "no work split fits this shape and workspace");
     }

@@ -143,7 +143,7 @@ def test_eight_member_group_with_split():
 
 def test_one_workspace_shared_in_stream_order():
     """One zero-filled workspace serves launches of different handles and plans
-    (decode splits, a tiled split, slices) issued back to back on one stream
+    (decode splits, a tiled split) issued back to back on one stream
     without synchronisation: each launch leaves its arrival counters at zero
     for the next, whatever plan that one has."""
     cases = [gen.random_case(60, 16, 9728, 2560), gen.random_case(61, 130, 1152, 496),
@@ -182,7 +182,7 @@ def test_small_workspace_gives_a_plan_that_fits():
         assert ref.compare(group_run([lin], c["x"], ws_bytes=nb)[0], y_ref)["ok"], nb
     x = dev(c["x"])
     with pytest.raises(qlin.QlinError) as e:
-        qlin.forward_group([lin], x, path=SKINNY, split_k=9, workspace=None)
+        qlin.forward_group([lin], x, path=SKINNY, split_k=11, workspace=None)
     assert e.value.code == qlin.QLIN_ERR_UNSUPPORTED
     lin.close()
 

@@ -84,3 +84,22 @@ def test_wide_layers_at_49_to_64_rows_need_no_scratch(planner, Ns, K, M, split):
     for ws in (-1, 0, 16 << 20):
         rc, p = plan(planner, Ns, K, M, split=split, ws=ws)
         assert rc == qlin.QLIN_OK and (p.S, p.ws_bytes, p.rows) == (1, 0, M), (ws, rc, p.S, p.ws_bytes, p.rows)
+
+
+@pytest.mark.parametrize("Ns,K,M,path,split,rc,chunks,rows", [
+    ([1264, 208, 292320], 6144, 27, SKINNY, 4, qlin.QLIN_ERR_UNSUPPORTED, 0, 0),   # its x and sums exceed LDS
+    ([431280], 16128, 30, SKINNY, 8, qlin.QLIN_ERR_UNSUPPORTED, 0, 0),
+    ([2560], 9728, 64, SKINNY, 10, qlin.QLIN_ERR_UNSUPPORTED, 0, 0),
+    ([2560], 9728, 64, SKINNY, 11, qlin.QLIN_OK, 11, 64),
+    ([3328, 257568, 96528, 80, 240, 96, 288, 144], 896, 35, AUTO, 4, qlin.QLIN_OK, 1, 35),   # dropped
+    ([580000], 256, 20, SKINNY, 2, qlin.QLIN_OK, 2, 16),       # more ranges than counters at 8 tiles each
+    ([580000], 256, 20, AUTO, 2, qlin.QLIN_OK, 2, 16),
+])
+def test_forced_splits_at_17_to_64_rows(planner, Ns, K, M, path, split, rc, chunks, rows):
+    """What a forced split accepts is bounded by LDS for its chunk of x and its
+    sums; the automatic path runs without the split instead."""
+    got, p = plan(planner, Ns, K, M, path=path, split=split)
+    assert got == rc, got
+    if rc == qlin.QLIN_OK:
+        assert (p.S, p.rows) == (chunks, rows)
+        assert planner.pc_wrong_work(*_members(Ns, K), path, split, M, -1) == 0
