@@ -143,8 +143,8 @@ __device__ inline void reduce_chunks(const FwdArgs &a, const WgWork &w) {
 }
 
 // Writes the workgroup's results from SETS partial sums per column tile in
-// LDS: set i of tile tl at row (i * tiles + tl) * rows of 16 fp32 columns
-// (sets that hold nothing for a tile are zero).  The sets of an item are added
+// LDS: set i of tile tl from row (i * tiles + tl) * rows of 16 fp32 columns, in
+// the order of sums_unit() (sets that hold nothing for a tile are zero).  The sets of an item are added
 // in order; with the whole K range covered (S == 1) the sum goes to y as bf16,
 // otherwise to the fp32 workspace, and the last of the S workgroups of this
 // column range adds the S partials in chunk order and writes y.  Every sum
@@ -175,7 +175,7 @@ __device__ inline void write_sums(const FwdArgs &a, const WgWork &w, const float
         float4 v[SETS];
 #pragma unroll
         for (int i = 0; i < SETS; ++i)
-            v[i] = *(const float4 *)(sums + ((size_t)(i * tiles + tl) * rows + m) * 16 + 4 * qq);
+            v[i] = *(const float4 *)(sums + (size_t)(i * tiles + tl) * rows * 16 + 4 * sums_unit(m, qq));
         float s[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < SETS; ++i) {

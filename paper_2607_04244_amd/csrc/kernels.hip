@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
             // straight-line path)
             if (__builtin_expect(kbl == (uint32_t)w.Kc - 1u || u == (uint32_t)u1 - 1u, 0)) {
                 // D of the 16x16 op: lane l holds rows n = 4(l >> 4) + v of column m = l & 15
-                *(v4f *)(slots + ((size_t)(wave * w.Tn + tl) * MR + lm) * 16 + 4 * lg) = acc;
+                *(v4f *)(slots + (size_t)(wave * w.Tn + tl) * MR * 16 + 4 * sums_unit(lm, lg)) = acc;
                 acc = v4f{0, 0, 0, 0};
             }
         };
@@ -477,7 +477,7 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
     // D of the 16x16 op: lane l holds rows n = 4(l >> 4) + v of column m = l & 15
 #pragma unroll
     for (int t = 0; t < TN; ++t)
-        if (t < Tn) *(v4f *)(slots + (((size_t)wave * TN + t) * 16 + lm) * 16 + 4 * lg) = acc[t];
+        if (t < Tn) *(v4f *)(slots + ((size_t)wave * TN + t) * 256 + 4 * sums_unit(lm, lg)) = acc[t];
     lds_barrier();
     write_sums<kWaves>(a, w, slots, TN, 16);
 }
@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
                     t4[r] = v;
                 }
                 if ((lane & 0x33) == 0)
-                    *(float4 *)(slots + (((size_t)wave * TN + t) * MV + m) * 16 + 4 * b2) =
+                    *(float4 *)(slots + ((size_t)wave * TN + t) * MV * 16 + 4 * sums_unit(m, b2)) =
                         make_float4(t4[0], t4[1], t4[2], t4[3]);
             }
         }

@@ -19,7 +19,8 @@ namespace qlin {
 // and LDS bandwidth would bound the kernel from 32 rows on.  A unit is a group
 // (128 k) up to 64 rows and half a group beyond, where the x of a whole one
 // would take 32 MT of a lane's registers.  With whole groups a last round of
-// up to four gives each to two waves, 64 k each.
+// up to four gives each to two waves: every other tile each, or, of one tile,
+// 64 k each.
 //
 // The waves share nothing before the end: a wave stages its unit's x in LDS
 // of its own with direct-to-LDS loads (LDS only turns rows into operand
@@ -43,7 +44,13 @@ namespace qlin {
 // 13.3 / 15.4 (17.1 / 17.1), 512 x 2048 at 65 / 128 rows 4.3 / 5.2 (5.7 / 5.9).
 //
 // At the end the waves' sums are added in LDS in a fixed order: wave w + 4 to
-// wave w, then the four sums in order.
+// wave w, then the four sums in order; of a single round of shared groups each
+// pair of waves is one of the four.  LDS bandwidth bounds this end, 16 KB a tile
+// and m-tile: with sums in row order (four lanes to a bank), every wave's sums of
+// every tile and both waves of a pair loading all of a shared group's weights,
+// 512 x 19456 at 17 / 48 rows took 6.6 / 7.8 us, now 5.7 / 6.6 (1024 x 19456
+// 7.5 / 9.0, now 7.1 / 8.3).  The last round is code of its own: tests of a round's kind
+// in front of each tile's loads cost the whole rounds 0.4 us.
 //
 // x of a wave in LDS: 16-byte chunk c (k = 8 c) of row r at slot
 // 16 r + (c ^ (r & 15)), as in the tiled kernel, or, with half-group units,
@@ -54,6 +61,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool HG = MT > 4;                      // a wave's unit of K: half a group
     constexpr int KJ = HG ? 2 : 4;                   // 32-wide steps of k in a unit
+    constexpr bool kShareTiles = !HG && TN > 1;      // what the two waves of a shared last group divide
     constexpr int ROWS = 16 * MT, kHalf = kWaves / 2;
     constexpr uint32_t kWaveX = ROWS * KJ * 64;      // LDS bytes of a wave's x
     constexpr int NS = (TN + 3) / 4;                 // scale loads per group: four tiles each
@@ -67,8 +75,8 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     const int full = units / kWaves, rem = units % kWaves;
     const bool paired = !HG && rem <= kHalf;
     const int tail = paired ? wave >> 1 : wave;      // its unit among the last ones
-    const int nr = full + (tail < rem ? 1 : 0);
-    auto unit_of = [&](int r) { return r < full ? r * kWaves + wave : full * kWaves + tail; };
+    const bool last = tail < rem;                    // takes part in the last round
+    auto other = [&](int t) { return ((t ^ wave) & 1) != 0; };   // a tile of the other wave of its pair
     auto group_of = [&](int u) { return HG ? u >> 1 : u; };
     auto half_of = [&](int u) { return HG ? (uint32_t)(u & 1) : 0u; };
 
@@ -113,12 +121,14 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         words_t c[TN];
         uint32_t s[NS];
     };
-    auto load_w = [&](Unit &g, int u) {
+    enum Share { kWhole, kTiles, kHalves };          // a round's part of this wave: its unit, or of a shared one
+    auto load_w = [&](auto share, Unit &g, int u) {
         const int kb = group_of(u);
 #pragma unroll
         for (int i = 0; i < NS; ++i) g.s[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, sv[i], kb * kSzBlk, kWeightPolicy);
 #pragma unroll
         for (int t = 0; t < TN; ++t) {
+            if (share == kTiles && other(t)) continue;
             const uint32_t soff = (uint32_t)(min(t, w.Tn - 1) * a.Kb + kb) * 1024u;
             if constexpr (HG)
                 g.c[t] = __builtin_amdgcn_raw_buffer_load_b64(rc, lane * 16 + half_of(u) * 8, soff, kWeightPolicy);
@@ -141,9 +151,12 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         const ExtractConsts<F16> kx;
         const DeqSel<SYM, F16> dsel(lane);
         Unit g;
-        load_x(unit_of(0));
-        load_w(g, unit_of(0));
-        for (int r = 0; r < nr; ++r) {
+        auto request = [&](auto share, int u) {
+            load_x(u);
+            load_w(share, g, u);
+        };
+        // one round on what is in flight; `next` requests the round after it
+        auto round = [&](auto share, auto next) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this round's x is in LDS
             const Unit cur = g;
             v8bf xf[KJ][MT];
@@ -153,10 +166,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
                 for (int mt = 0; mt < MT; ++mt)
                     xf[j][mt] = __builtin_bit_cast(v8bf, xb[mt * 16 * kChunks + swizzle(lm, 4 * j + lg)]);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // and in registers: its LDS is free
-            if (r + 1 < nr) {
-                load_x(unit_of(r + 1));
-                load_w(g, unit_of(r + 1));
-            }
+            next();
             uint32_t sz[4 * NS];
 #pragma unroll
             for (int i = 0; i < NS; ++i) {                       // each tile's words to all lanes of its column
@@ -168,60 +178,85 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
                 sz[4 * i + 2] = o[0];
                 sz[4 * i + 3] = o[1];
             }
-            // all of the unit's k, or this wave's 64 of a shared last group
-            const bool lo = r < full || !paired || (wave & 1) == 0, hi = r < full || !paired || (wave & 1) == 1;
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
-                if (t >= w.Tn) continue;
+                if (t >= w.Tn || (share == kTiles && other(t))) continue;
                 const MfmaDeq d = dsel.setup(sz[t]);
-                auto word = [&](int j) {
+#pragma unroll
+                for (int j = 0; j < KJ; ++j) {
+                    if (share == kHalves && (j >> 1) != (wave & 1)) continue;
                     const v8bf wa = mfma_dequant<F16>(cur.c[t][j], d, kx);
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
                         acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[j][mt], acc[t][mt], 0, 0, 0);
-                };
-                if constexpr (HG) {
-                    word(0);
-                    word(1);
-                } else {
-                    if (lo) {
-                        word(0);
-                        word(1);
-                    }
-                    if (hi) {
-                        word(2);
-                        word(3);
-                    }
                 }
             }
+        };
+        using Whole = std::integral_constant<Share, kWhole>;
+        using Part = std::integral_constant<Share, kShareTiles ? kTiles : kHalves>;
+        auto request_last = [&] {
+            if (!last) return;
+            if (paired) request(Part{}, full * kWaves + tail);
+            else request(Whole{}, full * kWaves + tail);
+        };
+        if (full > 0) {
+            request(Whole{}, wave);
+            for (int r = 1; r < full; ++r) round(Whole{}, [&] { request(Whole{}, r * kWaves + wave); });
+            round(Whole{}, request_last);
+        } else {
+            request_last();
+        }
+        if (last) {
+            if (paired) round(Part{}, [] {});
+            else round(Whole{}, [] {});
         }
     };
-    if (nr > 0) {
+    if (full > 0 || last) {
         if (w.f16) walk(std::true_type{});
         else walk(std::false_type{});
     }
 
-    // sums: [wave w < 4][tile][row][16 columns] fp32 in LDS, over the x.  D of
-    // the 16x16 op: lane l holds columns 4 (l >> 4) + v of row l & 15
+    // sums: [set < 4][tile][row][16 columns] fp32 in LDS, over the x, in the order
+    // of sums_unit().  D of the 16x16 op: lane l holds columns 4 (l >> 4) + v of row l & 15
     lds_barrier();
     float *sums = (float *)smem;
-    auto at = [&](int t, int mt) {
-        return sums + ((size_t)((wave & (kHalf - 1)) * TN + t) * ROWS + 16 * mt + lm) * 16 + 4 * lg;
+    auto at = [&](int set, int t, int mt) {
+        return (v4f *)(sums + (size_t)(set * TN + t) * ROWS * 16 + 4 * sums_unit(16 * mt + lm, lg));
     };
-    if (wave >= kHalf) {
+    if (kShareTiles && paired && full == 0) {
+        // one round of shared groups: the pairs are the sets, each tile in one wave of a pair
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                if (t < w.Tn) *(v4f *)at(t, mt) = acc[t][mt];
-    }
-    lds_barrier();
-    if (wave < kHalf) {
+                if (t < w.Tn && !other(t)) *at(wave >> 1, t, mt) = acc[t][mt];
+    } else {
+        // wave w + 4 to wave w (no sums in waves past the last unit of a single round)
+        auto busy = [&](int wv) { return full > 0 || (paired ? wv >> 1 : wv) < rem; };
+        const int set = wave & (kHalf - 1);
+        if (wave >= kHalf && busy(wave)) {
 #pragma unroll
-        for (int t = 0; t < TN; ++t)
+            for (int t = 0; t < TN; ++t)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                if (t < w.Tn) *(v4f *)at(t, mt) = acc[t][mt] + *(const v4f *)at(t, mt);
+                for (int mt = 0; mt < MT; ++mt)
+                    if (t < w.Tn) *at(set, t, mt) = acc[t][mt];
+        }
+        lds_barrier();
+        if (wave < kHalf) {
+            if (busy(wave + kHalf)) {
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        if (t < w.Tn) *at(set, t, mt) = acc[t][mt] + *at(set, t, mt);
+            } else {
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+                        if (t < w.Tn) *at(set, t, mt) = acc[t][mt];
+            }
+        }
     }
     lds_barrier();
     write_sums<kHalf>(a, w, sums, TN, ROWS);

@@ -86,6 +86,13 @@ __host__ __device__ inline int gn_chunk(int b, int Gn, uint32_t inv, int shift) 
     return (int)((uint32_t)(((uint64_t)(uint32_t)b * inv) >> 32) >> shift) + (Gn == 1 ? b : 0);
 }
 
+// Partial sums in LDS: a tile's rows of 16 fp32 columns in 16-byte units (quarter
+// rows), quarter q of row m at unit sums_unit(m, q).  The exclusive-or spreads
+// both the matrix cores' results (lane l holds quarter l >> 4 of row l & 15: in
+// row order its 16 lanes of a quarter would be 64 bytes apart and share a quarter
+// of the banks) and the reads in row order over all banks.
+__host__ __device__ inline int sums_unit(int m, int q) { return 4 * m + (q ^ ((m >> 2) & 3)); }
+
 // TILED kernel (prefill-sized M): a workgroup of kTiledWaves x WS waves
 // computes a (16 MSW) x (64 NT) block of y; wave w owns all 16 MSW rows of
 // column tiles NW w .. NW w + NW - 1 (NW = NT / WS).  Block shapes (MSW, NT): 128 x 256

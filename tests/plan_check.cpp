@@ -91,4 +91,20 @@ int64_t pc_wrong_chunks(int Gn, int64_t S) {
     return wrong;
 }
 
+// Most 16-byte units on one LDS bank group (of 16) among 16 lanes in a row, for
+// the matrix cores' results (lane l: quarter l >> 4 of row l & 15) and for reads
+// in row order, over rows rows.
+int pc_sums_conflicts(int rows) {
+    int worst = 0;
+    for (int first = 0; first < rows * 4; first += 16)
+        for (int order = 0; order < 2; ++order) {
+            int n[16] = {};
+            for (int i = first; i < first + 16; ++i) {
+                const int u = order ? sums_unit(i >> 2, i & 3) : sums_unit(first / 64 * 16 + i % 16, first / 16 % 4);
+                worst = std::max(worst, ++n[u & 15]);
+            }
+        }
+    return worst;
+}
+
 }  // extern "C"

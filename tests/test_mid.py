@@ -35,6 +35,19 @@ def test_rounds_tiles_and_rows_end_unevenly(M, Kb, N):
         lin.close()
 
 
+@pytest.mark.parametrize("M", [17, 48, 64])
+@pytest.mark.parametrize("Kb,N", [(1, 8208), (2, 12304), (4, 19456), (5, 8192), (7, 12288), (8, 8208), (11, 8208),
+                                  (12, 4112)])
+def test_last_groups_shared_by_tile(M, Kb, N):
+    """Two and more tiles a workgroup: the waves of a pair take every other tile
+    of a shared last group, alone (up to 4 groups) or after whole rounds; single
+    rounds with waves that have no group (5 to 7)."""
+    c = gen.random_case(M * 1000 + Kb * 10 + N, M, 128 * Kb, N)
+    lin = make(c)
+    assert_close(run(lin, c["x"], SKINNY), oracle(c), f"M={M} Kb={Kb} N={N}")
+    lin.close()
+
+
 @pytest.mark.parametrize("M", [65, 80, 81, 96, 97, 112, 113, 128, 129, 144])
 @pytest.mark.parametrize("Kb,N", [(3, 48), (4, 16), (5, 208), (9, 224), (13, 4112)])
 def test_half_group_units_end_unevenly(M, Kb, N):

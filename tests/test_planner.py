@@ -103,3 +103,9 @@ def test_forced_splits_at_17_to_64_rows(planner, Ns, K, M, path, split, rc, chun
     if rc == qlin.QLIN_OK:
         assert (p.S, p.rows) == (chunks, rows)
         assert planner.pc_wrong_work(*_members(Ns, K), path, split, M, -1) == 0
+
+
+def test_partial_sums_in_lds_spread_over_the_banks(planner):
+    """The 16-byte writes and reads of the partial sums by 16 neighbouring lanes
+    touch every bank once (in row order the writes would meet four to a bank)."""
+    assert planner.pc_sums_conflicts(144) == 1
