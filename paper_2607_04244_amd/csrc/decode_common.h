@@ -1,10 +1,26 @@
-// Device code shared by the decode kernels (kernels.hip, mid.hip): a
+// Device code shared by the decode kernels (kernels.hip, mid.hip; tiled.hip uses on_route): a
 // workgroup's share of a launch, and the exchange of split-K partial sums.
 #pragma once
 
 #include "device_common.h"
 
+#include <type_traits>
+
 namespace qlin {
+
+// Calls walk(std::bool_constant<f16 route>): for a mixed launch by the member's
+// route (uniform in the workgroup: its tiles belong to one member).  A walk
+// includes its first loads, so that none in flight is copied between the two
+// routes' registers.
+template <Route R, typename Walk>
+__device__ inline void on_route(bool member_f16, const Walk &walk) {
+    if constexpr (R == kRouteMixed) {
+        if (member_f16) walk(std::true_type{});
+        else walk(std::false_type{});
+    } else {
+        walk(std::bool_constant<R == kRouteF16>{});
+    }
+}
 
 // Column range, member and K chunk of workgroup `bid`: chunk c, range jn
 // (over all members), the member's tiles [t0, t0 + Tn) and groups
@@ -15,13 +31,14 @@ struct WgWork {
     const void *sz;
     uint16_t *y;
     int N;
-    int f16;
+    bool f16;
     float unscale;           // what the sums are multiplied by before their rounding (F16 route)
 };
 // Everything here is wave-uniform scalar work at the start of the kernel:
 // the arguments arrive in one batch of scalar loads (the range starts are one
 // contiguous array, every index static, and the chunk needs no division),
 // then the member's fields in one more.
+template <Route R>
 __device__ inline WgWork wg_work(const FwdArgs &a, int bid) {
     WgWork w;
     w.c = gn_chunk(bid, a.Gn, a.inv_gn, a.gn_shift);
@@ -41,8 +58,8 @@ __device__ inline WgWork wg_work(const FwdArgs &a, int bid) {
     w.sz = f.sz;
     w.y = f.y;
     w.N = f.N;
-    w.f16 = f.f16;
-    w.unscale = f.f16 ? kF16Unscale : 1.0f;
+    w.f16 = R == kRouteMixed ? f.f16 != 0 : R == kRouteF16;
+    w.unscale = w.f16 ? kF16Unscale : 1.0f;
     const int j = w.jn - g0;
     w.t0 = j * f.Nq + min(j, f.Nr);
     w.Tn = f.Nq + (j < f.Nr ? 1 : 0);

@@ -37,7 +37,6 @@
 #include <algorithm>
 #include <cstdio>
 #include <mutex>
-#include <type_traits>
 
 namespace qlin {
 
@@ -204,13 +203,13 @@ __device__ inline void wave_range(int U, int i, int &u0, int &u1) {
 // one address plus immediate offsets (4 j slots).  XR = staged rows (the
 // next power of two >= M).  Lane l reads row min(l & 15, M - 1); pad slots and
 // rows >= M hold copies and are never read.
-template <int XR, bool SYM>
+template <int XR, bool SYM, Route R>
 __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int MR = 16;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps the walk on the scalar unit
-    const WgWork w = wg_work(a, blockIdx.x);
+    const WgWork w = wg_work<R>(a, blockIdx.x);
     uint4 *xs = (uint4 *)smem;
     const int n8 = w.Kc * 16;                         // 16-byte chunks per row of the x chunk
     const int nslots = XR * (n8 + 1);
@@ -271,9 +270,6 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
     // slot is 16 kbl + 4 j + xoff
     const int xoff = min(lm, a.M - 1) * (n8 + 1) + lg;
 
-    // the whole walk exists once per dequantization route (uniform in the
-    // workgroup: its tiles belong to one member), its first loads included,
-    // so that none in flight is copied between the routes' registers
     auto walk = [&](auto route) {
         constexpr bool F16 = decltype(route)::value;
         const ExtractConsts<F16> kx;
@@ -337,8 +333,7 @@ __global__ void __launch_bounds__(kThreads) k_skinny(FwdArgs a) {
         for (int d = 0; d < kDepth; ++d)
             if (u + d < u1) consume((uint32_t)(u + d), cb[d], sb[d]);
     };
-    if (w.f16) walk(std::true_type{});
-    else walk(std::false_type{});
+    on_route<R>(w.f16, walk);
     lds_barrier();
     write_sums<kWaves>(a, w, slots, w.Tn, MR);
 }
@@ -419,13 +414,13 @@ __device__ inline v8bf load_xfrag(const FwdArgs &a, int kb, int j, int lane) {
                                                       8 * (lane >> 4)));
 }
 
-template <int TN, bool SYM>
+template <int TN, bool SYM, Route R>
 __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *slots = (float *)smem;                  // [kWaves][TN][16][16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const WgWork w = wg_work(a, blockIdx.x);
+    const WgWork w = wg_work<R>(a, blockIdx.x);
     const int Tn = w.Tn;
     int u0, u1;
     wave_range(Tn * w.Kc, wave, u0, u1);
@@ -435,7 +430,7 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
 #pragma unroll
     for (int t = 0; t < TN; ++t) acc[t] = v4f{0, 0, 0, 0};
 
-    auto walk = [&](auto route) {            // once per dequantization route, as in k_skinny
+    auto walk = [&](auto route) {
         constexpr bool F16 = decltype(route)::value;
         const ExtractConsts<F16> kx;
         const DeqSel<SYM, F16> dsel(lane);
@@ -470,10 +465,7 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
         MfmaGroup<TN> ring[ring_groups<TN>()];
         group_ring(wg.kg0, wg.kg1, ring, load_group, compute_group);
     };
-    if (u0 < u1) {
-        if (w.f16) walk(std::true_type{});
-        else walk(std::false_type{});
-    }
+    if (u0 < u1) on_route<R>(w.f16, walk);
     // D of the 16x16 op: lane l holds rows n = 4(l >> 4) + v of column m = l & 15
 #pragma unroll
     for (int t = 0; t < TN; ++t)
@@ -494,14 +486,14 @@ struct GemvGroup {
     uint32_t x[MV][4];
 };
 
-template <int MV, int TN, bool SYM>
+template <int MV, int TN, bool SYM, Route R>
 __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *slots = (float *)smem;                  // [kWaves][TN][MV][16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ExtractConsts<false> kx;
-    const WgWork w = wg_work(a, blockIdx.x);
+    const WgWork w = wg_work<R>(a, blockIdx.x);
     const int Tn = w.Tn;
     int u0, u1;
     wave_range(Tn * w.Kc, wave, u0, u1);
@@ -798,48 +790,55 @@ hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool 
     return hipGetLastError();
 }
 
-template <int TN, bool SYM>
+template <int TN, bool SYM, Route R>
 static FwdKernel pick_regs(int kern, int mrows) {
-    if (kern == kKernMfma16) return k_mfma16<TN, SYM>;
+    if (kern == kKernMfma16) return k_mfma16<TN, SYM, R>;
     if constexpr (TN <= kTnMaxGemv) {
         switch (mrows) {
-            case 1: return k_gemv4<1, TN, SYM>;
-            case 2: return k_gemv4<2, TN, SYM>;
-            case 3: return k_gemv4<3, TN, SYM>;
-            case 4: return k_gemv4<4, TN, SYM>;
+            case 1: return k_gemv4<1, TN, SYM, R>;
+            case 2: return k_gemv4<2, TN, SYM, R>;
+            case 3: return k_gemv4<3, TN, SYM, R>;
+            case 4: return k_gemv4<4, TN, SYM, R>;
         }
+    }
+    return nullptr;
+}
+
+template <bool SYM, Route R>
+static FwdKernel pick(int kern, int mrows, int tn) {
+    if (kern == kKernStaged) {        // tn = staged rows XR
+        switch (tn) {
+            case 1: return k_skinny<1, SYM, R>;
+            case 2: return k_skinny<2, SYM, R>;
+            case 4: return k_skinny<4, SYM, R>;
+            case 8: return k_skinny<8, SYM, R>;
+            case 16: return k_skinny<16, SYM, R>;
+        }
+        return nullptr;
+    }
+    switch (tn) {
+        case 1: return pick_regs<1, SYM, R>(kern, mrows);
+        case 2: return pick_regs<2, SYM, R>(kern, mrows);
+        case 3: return pick_regs<3, SYM, R>(kern, mrows);
+        case 4: return pick_regs<4, SYM, R>(kern, mrows);
+        case 5: return pick_regs<5, SYM, R>(kern, mrows);
+        case 6: return pick_regs<6, SYM, R>(kern, mrows);
+        case 7: return pick_regs<7, SYM, R>(kern, mrows);
+        case 8: return pick_regs<8, SYM, R>(kern, mrows);
     }
     return nullptr;
 }
 
 template <bool SYM>
-static FwdKernel pick(int kern, int mrows, int tn) {
-    if (kern == kKernStaged) {        // tn = staged rows XR
-        switch (tn) {
-            case 1: return k_skinny<1, SYM>;
-            case 2: return k_skinny<2, SYM>;
-            case 4: return k_skinny<4, SYM>;
-            case 8: return k_skinny<8, SYM>;
-            case 16: return k_skinny<16, SYM>;
-        }
-        return nullptr;
-    }
-    switch (tn) {
-        case 1: return pick_regs<1, SYM>(kern, mrows);
-        case 2: return pick_regs<2, SYM>(kern, mrows);
-        case 3: return pick_regs<3, SYM>(kern, mrows);
-        case 4: return pick_regs<4, SYM>(kern, mrows);
-        case 5: return pick_regs<5, SYM>(kern, mrows);
-        case 6: return pick_regs<6, SYM>(kern, mrows);
-        case 7: return pick_regs<7, SYM>(kern, mrows);
-        case 8: return pick_regs<8, SYM>(kern, mrows);
-    }
-    return nullptr;
+static FwdKernel pick_route(int kern, int mrows, int tn, Route route) {
+    return route == kRouteMixed  ? pick<SYM, kRouteMixed>(kern, mrows, tn)
+           : route == kRouteF16 ? pick<SYM, kRouteF16>(kern, mrows, tn)
+                                : pick<SYM, kRouteBf16>(kern, mrows, tn);
 }
 
-static FwdKernel pick_kernel(int kern, int mrows, int tn, bool symmetric) {
-    if (kern == kKernMid) return pick_mid(mrows, tn, symmetric);
-    return symmetric ? pick<true>(kern, mrows, tn) : pick<false>(kern, mrows, tn);
+static FwdKernel pick_kernel(int kern, int mrows, int tn, bool symmetric, Route route) {
+    if (kern == kKernMid) return pick_mid(mrows, tn, symmetric);     // any route
+    return symmetric ? pick_route<true>(kern, mrows, tn, route) : pick_route<false>(kern, mrows, tn, route);
 }
 
 const char *kernel_name(int kern, int mrows, int tn, bool symmetric) {
@@ -853,28 +852,26 @@ const char *kernel_name(int kern, int mrows, int tn, bool symmetric) {
 }
 
 hipError_t prepare_kernels() {
-    for (int sym = 0; sym < 2; ++sym) {
-        for (int tn = 1; tn <= kTnMax; ++tn) {
-            (void)hipFuncSetAttribute((const void *)pick_kernel(kKernMfma16, 16, tn, sym),
+    auto allow = [](int kern, int mrows, int tn, bool sym) {
+        for (Route r : {kRouteBf16, kRouteF16, kRouteMixed})
+            (void)hipFuncSetAttribute((const void *)pick_kernel(kern, mrows, tn, sym, r),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
-            for (int mv = 1; tn <= kTnMaxGemv && mv <= kMaxGemvM; ++mv)
-                (void)hipFuncSetAttribute((const void *)pick_kernel(kKernGemv, mv, tn, sym),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+    };
+    for (bool sym : {false, true}) {
+        for (int tn = 1; tn <= kTnMax; ++tn) {
+            allow(kKernMfma16, 16, tn, sym);
+            for (int mv = 1; tn <= kTnMaxGemv && mv <= kMaxGemvM; ++mv) allow(kKernGemv, mv, tn, sym);
         }
         for (int mt = 2; mt <= kMidTilesM; ++mt)
-            for (int tn = 1; tn <= mid_tiles_max(mt); ++tn)
-                (void)hipFuncSetAttribute((const void *)pick_mid(16 * mt, tn, sym),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
-        for (int xr : {1, 2, 4, 8, 16})
-            (void)hipFuncSetAttribute((const void *)pick_kernel(kKernStaged, 0, xr, sym),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);
+            for (int tn = 1; tn <= mid_tiles_max(mt); ++tn) allow(kKernMid, 16 * mt, tn, sym);
+        for (int xr : {1, 2, 4, 8, 16}) allow(kKernStaged, 0, xr, sym);
     }
     return hipSuccess;
 }
 
-hipError_t launch_forward(int kern, int mrows, int tn, bool symmetric, int grid, size_t lds,
+hipError_t launch_forward(int kern, int mrows, int tn, bool symmetric, Route route, int grid, size_t lds,
                           const FwdArgs &a, hipStream_t st) {
-    FwdKernel k = pick_kernel(kern, mrows, tn, symmetric);
+    FwdKernel k = pick_kernel(kern, mrows, tn, symmetric, route);
     if (!k) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3(grid), dim3(kThreads), lds, st, a);
     return hipGetLastError();

@@ -733,6 +733,13 @@ int workspace_need(const Target &t, int path, int64_t split_k, int64_t M, size_t
     return rc;
 }
 
+// The dequantization route of a launch over the members of t.
+Route route_of(const Target &t) {
+    int n = 0;
+    for (int i = 0; i < t.nmem; ++i) n += t.mem[i]->f16 ? 1 : 0;
+    return n == t.nmem ? kRouteF16 : n == 0 ? kRouteBf16 : kRouteMixed;
+}
+
 // Launch arguments of a decode-kernel plan for M rows (M <= 64) at x, with
 // member i writing ys[i]; the workspace holds counters then partials.
 FwdArgs fwd_args(const Target &t, const Plan &p, int64_t M, const uint16_t *x, uint16_t *const *ys,
@@ -829,7 +836,6 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
     a.counters = (uint32_t *)ws;
     a.ws = ws_partials(ws);
     a.ws_bytes = ws_partial_bytes(ws, ws_bytes);
-    a.nmem = t.nmem;
     a.f16 = 0;
     int gb0 = 0;
     for (int i = 0; i < kMaxMembers; ++i) {
@@ -849,7 +855,7 @@ int launch_tiled_rows(const Target &t, const Plan &p, int64_t M, const uint16_t 
         a.gb0[i] = gb0;
         gb0 += (h->Nt + 4 * p.tn - 1) / (4 * p.tn);
     }
-    const hipError_t e = launch_tiled(t.symmetric, TiledShape{p.mrows / 16, p.tn}, a, p.grid, st);
+    const hipError_t e = launch_tiled(t.symmetric, route_of(t), TiledShape{p.mrows / 16, p.tn}, a, p.grid, st);
     return e == hipSuccess ? QLIN_OK : hip_fail(e, "tiled launch");
 }
 
@@ -876,7 +882,7 @@ int launch_all(const Target &t, int path, int64_t split_k, int64_t M, const uint
             if ((rc = launch_tiled_rows(t, p, Ms, x + m0 * t.K, yk, ws, ws_bytes, st)) != QLIN_OK) return rc;
         } else {
             const FwdArgs a = fwd_args(t, p, Ms, x, ys, ws, ws_bytes, m0);
-            const hipError_t e = launch_forward(p.kern, p.mrows, p.tn, t.symmetric, p.grid, p.lds, a, st);
+            const hipError_t e = launch_forward(p.kern, p.mrows, p.tn, t.symmetric, route_of(t), p.grid, p.lds, a, st);
             if (e != hipSuccess) return hip_fail(e, "forward launch");
         }
         m0 += Ms;
@@ -1028,7 +1034,8 @@ int run_forward(qlin_s *h, int path, int64_t split_k, int64_t M, const uint16_t 
     const CachedPlan *cp = (path == kAuto && split_k == 0 && M <= kMaxSkinnyM) ? &h->auto_plans[M - 1] : nullptr;
     if (cp && cp->ok && cp->p.rows >= M) {     // the automatic plan, computed at creation: one launch
         const FwdArgs a = fwd_args(t, cp->p, M, x, ys, h->ws, h->ws_bytes, 0);
-        const hipError_t e = launch_forward(cp->p.kern, cp->p.mrows, cp->p.tn, t.symmetric, cp->p.grid, cp->p.lds, a, st);
+        const hipError_t e = launch_forward(cp->p.kern, cp->p.mrows, cp->p.tn, t.symmetric, route_of(t), cp->p.grid,
+                                            cp->p.lds, a, st);
         if (e != hipSuccess) return hip_fail(e, "forward launch");
         rc = QLIN_OK;
     } else {

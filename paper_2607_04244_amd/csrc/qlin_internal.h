@@ -37,6 +37,13 @@ enum Kern {
     kKernTiled = 3     // k_tiled: any M, 128 x 256 output blocks, x and weights staged in LDS (TILED path)
 };
 
+// The dequantization routes of a launch (device_common.h): that of all its
+// members, or kRouteMixed, whose kernels hold both and choose by the member.  The
+// choice at run time and the second copy of the walk cost a launch of few blocks
+// up to 6 % (1152 x 5136 at 8 rows 4.42 -> 4.70 us), so only groups that need it
+// pay.
+enum Route { kRouteBf16 = 0, kRouteF16 = 1, kRouteMixed = 2 };
+
 // Arguments of one forward launch of the decode kernels, over one linear or
 // over a group of up to kMaxMembers linears that share x (same K).  The K
 // range [0, Kb) of groups is cut into S chunks and the column tiles of the
@@ -51,7 +58,7 @@ struct FwdMember {
     uint16_t *y;            // [M][N] bf16
     int N;                  // output columns
     int Nq, Nr;
-    int f16;                // the handle's dequantization route (device_common.h)
+    int f16;                // the handle's dequantization route (for kRouteMixed)
 };
 struct FwdArgs {
     const uint16_t *x;      // [M][K] bf16, shared by all members
@@ -125,11 +132,14 @@ struct TiledArgs {
     float *ws;              // S > 1: fp32 partial blocks, Gn Mt S of 16 MSW x 64 NT
     uint32_t *counters;     // S > 1: [Gn Mt] arrival counters, zero between launches
     uint32_t ws_bytes;      // size of ws
-    int nmem;
-    uint32_t f16;           // bit i: dequantization route of member i (device_common.h)
+    uint32_t f16;           // bit i: dequantization route of member i (for kRouteMixed)
     int gb0[kMaxMembers];   // first column block of each member (Gn for absent members)
     TiledMember mem[kMaxMembers];
 };
+// What a workgroup reads of the arguments lies in the first two 64-byte lines and
+// its member's one: with members across lines a launch took 0.3 us longer (512 x
+// 19456 at 200 rows 12.5 -> 12.8 us).
+static_assert(offsetof(TiledArgs, gb0) == 64 && offsetof(TiledArgs, mem) == 96 && sizeof(TiledMember) == 32, "");
 
 // Rows of x a SKINNY workgroup keeps in LDS for M rows (M <= 64): the next
 // power of two >= M up to 16, else whole m-tiles of 16.
@@ -169,7 +179,7 @@ FwdKernel pick_mid(int mrows, int tn, bool symmetric);
 // Host launchers (kernels.hip).  Each returns the launch status.
 hipError_t launch_repack(const uint32_t *canon, const uint16_t *scales, const uint16_t *zeros,
                          uint4 *codes, void *sz, int K, int N, bool symmetric, bool f16, hipStream_t st);
-hipError_t launch_forward(int kern, int mrows, int tn, bool symmetric, int grid, size_t lds,
+hipError_t launch_forward(int kern, int mrows, int tn, bool symmetric, Route route, int grid, size_t lds,
                           const FwdArgs &a, hipStream_t st);
 hipError_t launch_unpack(const uint4 *codes, uint8_t *q, int K, int N, hipStream_t st);
 hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool symmetric, bool f16,
@@ -177,7 +187,7 @@ hipError_t launch_dequant(int routine, const uint4 *codes, const void *sz, bool 
 hipError_t prepare_kernels();     // per-process attribute setup (LDS limits)
 hipError_t launch_quantize(const uint16_t *w, const uint16_t *scales, const uint16_t *zeros, uint32_t *packed,
                            int K, int N, hipStream_t st);
-hipError_t launch_tiled(bool symmetric, TiledShape shape, const TiledArgs &a, int grid, hipStream_t st);
+hipError_t launch_tiled(bool symmetric, Route route, TiledShape shape, const TiledArgs &a, int grid, hipStream_t st);
 hipError_t launch_stream_read(const void *buf, size_t bytes, int grid, uint32_t *sink, hipStream_t st);
 const char *kernel_name(int kern, int mrows, int tn, bool symmetric);
 

@@ -7,9 +7,7 @@
 // dequantizing 4x4x4 products feed vector instructions, and with results in
 // accumulation registers every value would need a copy back.
 
-#include "device_common.h"
-
-#include <type_traits>
+#include "decode_common.h"
 
 namespace qlin {
 
@@ -53,7 +51,7 @@ namespace qlin {
 // offset (block S + c) BM BN, element (ms, tile, lane) at 4 ((ms 4 NT + tile)
 // 64 + lane): one 16-byte access per lane and product.
 
-template <bool SYM, int MSW, int NT, int WS, bool SPLIT>
+template <bool SYM, Route R, int MSW, int NT, int WS, bool SPLIT>
 __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) k_tiled(TiledArgs a) {
     constexpr int kWavesWg = kTiledWaves * WS;
     constexpr int BM = 16 * MSW;
@@ -198,8 +196,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     // LDS slot of this lane's operand read: row 16 ms + lm, chunk 4 j + lg
     auto xslot = [&](int ms, int j) { return ms * 256 + lm * 16 + ((4 * j + lg) ^ lm); };
 
-    // one step's products; the K walk below exists once per dequantization
-    // route (uniform in the workgroup: its tiles belong to one member)
+    // one step's products
     auto compute = [&](const auto &kx, const auto &dsel, int buf, const uint4 (&cw)[NW], const uint32_t (&sw)[NW]) {
         MfmaDeq d[NW];
 #pragma unroll
@@ -248,7 +245,8 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
         const ExtractConsts<F16> kx;
         const DeqSel<SYM, F16> dsel(lane);
         int buf = 0;
-        for (int kb = g0; kb <= g1; ++kb) {
+        int kb = g0;
+        do {             // (a chunk holds a group: without a path around the loop the sums are zeroed once)
             asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * kIssued) : "memory");
             uint4 cw[NW];
             uint32_t sw[NW];
@@ -267,11 +265,10 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
             }
             compute(kx, dsel, buf, cw, sw);
             buf = buf == S - 1 ? 0 : buf + 1;
-        }
+        } while (++kb <= g1);
     };
-    const bool f16 = (a.f16 >> m) & 1u;
-    if (f16) walk(std::true_type{});
-    else walk(std::false_type{});
+    const bool f16 = R == kRouteMixed ? (a.f16 >> m) & 1u : R == kRouteF16;
+    on_route<R>(f16, walk);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the reloads past the end
 
     if constexpr (SPLIT) {
@@ -352,26 +349,33 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
     }
 }
 
-template <bool SYM, bool SPLIT>
+template <bool SYM, Route R, bool SPLIT>
 hipError_t launch_tiled_kernel(TiledShape sh, const TiledArgs &a, int grid, hipStream_t st) {
     const dim3 g(grid);
     const dim3 b(kTiledWaves * 64 * tiled_wsplit(sh));
-    if (sh.msw == 8 && sh.nt == 4) hipLaunchKernelGGL((k_tiled<SYM, 8, 4, tiled_wsplit({8, 4}), SPLIT>), g, b, 0, st, a);
-    else if (sh.msw == 4 && sh.nt == 2) hipLaunchKernelGGL((k_tiled<SYM, 4, 2, tiled_wsplit({4, 2}), SPLIT>), g, b, 0, st, a);
-    else if (sh.msw == 6 && sh.nt == 4) hipLaunchKernelGGL((k_tiled<SYM, 6, 4, tiled_wsplit({6, 4}), SPLIT>), g, b, 0, st, a);
+    if (sh.msw == 8 && sh.nt == 4) hipLaunchKernelGGL((k_tiled<SYM, R, 8, 4, tiled_wsplit({8, 4}), SPLIT>), g, b, 0, st, a);
+    else if (sh.msw == 4 && sh.nt == 2) hipLaunchKernelGGL((k_tiled<SYM, R, 4, 2, tiled_wsplit({4, 2}), SPLIT>), g, b, 0, st, a);
+    else if (sh.msw == 6 && sh.nt == 4) hipLaunchKernelGGL((k_tiled<SYM, R, 6, 4, tiled_wsplit({6, 4}), SPLIT>), g, b, 0, st, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 // The whole-K kernel is a separate instantiation from the K-split one, so
 // that the split's epilogue does not weigh on its register allocation.
-template <bool SYM>
-hipError_t launch_tiled_sym(TiledShape sh, const TiledArgs &a, int grid, hipStream_t st) {
-    return a.S > 1 ? launch_tiled_kernel<SYM, true>(sh, a, grid, st) : launch_tiled_kernel<SYM, false>(sh, a, grid, st);
+template <bool SYM, Route R>
+hipError_t launch_tiled_route(TiledShape sh, const TiledArgs &a, int grid, hipStream_t st) {
+    return a.S > 1 ? launch_tiled_kernel<SYM, R, true>(sh, a, grid, st) : launch_tiled_kernel<SYM, R, false>(sh, a, grid, st);
 }
 
-hipError_t launch_tiled(bool symmetric, TiledShape shape, const TiledArgs &a, int grid, hipStream_t st) {
-    return symmetric ? launch_tiled_sym<true>(shape, a, grid, st) : launch_tiled_sym<false>(shape, a, grid, st);
+template <bool SYM>
+hipError_t launch_tiled_sym(Route route, TiledShape sh, const TiledArgs &a, int grid, hipStream_t st) {
+    return route == kRouteMixed  ? launch_tiled_route<SYM, kRouteMixed>(sh, a, grid, st)
+           : route == kRouteF16 ? launch_tiled_route<SYM, kRouteF16>(sh, a, grid, st)
+                                : launch_tiled_route<SYM, kRouteBf16>(sh, a, grid, st);
+}
+
+hipError_t launch_tiled(bool symmetric, Route route, TiledShape shape, const TiledArgs &a, int grid, hipStream_t st) {
+    return symmetric ? launch_tiled_sym<true>(route, shape, a, grid, st) : launch_tiled_sym<false>(route, shape, a, grid, st);
 }
 
 }  // namespace qlin

@@ -6,7 +6,7 @@
 namespace qlin {
 hipError_t launch_repack(const uint32_t *, const uint16_t *, const uint16_t *, uint4 *, void *, int, int, bool, bool,
                          hipStream_t) { return hipSuccess; }
-hipError_t launch_forward(int, int, int, bool, int, size_t, const FwdArgs &, hipStream_t) { return hipSuccess; }
+hipError_t launch_forward(int, int, int, bool, Route, int, size_t, const FwdArgs &, hipStream_t) { return hipSuccess; }
 hipError_t launch_unpack(const uint4 *, uint8_t *, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_dequant(int, const uint4 *, const void *, bool, bool, uint16_t *, int, int, hipStream_t) {
     return hipSuccess;
@@ -15,7 +15,7 @@ hipError_t prepare_kernels() { return hipSuccess; }
 hipError_t launch_quantize(const uint16_t *, const uint16_t *, const uint16_t *, uint32_t *, int, int, hipStream_t) {
     return hipSuccess;
 }
-hipError_t launch_tiled(bool, TiledShape, const TiledArgs &, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_tiled(bool, Route, TiledShape, const TiledArgs &, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_stream_read(const void *, size_t, int, uint32_t *, hipStream_t) { return hipSuccess; }
 const char *kernel_name(int, int, int, bool) { return ""; }
 hipError_t static_scratch_setup(int, hipStream_t) { return hipSuccess; }
@@ -89,6 +89,18 @@ int64_t pc_wrong_chunks(int Gn, int64_t S) {
     for (int64_t c = 0; c < S; ++c)
         for (int64_t b : {c * Gn, c * Gn + Gn / 2, c * Gn + Gn - 1}) wrong += gn_chunk((int)b, Gn, inv, shift) != c;
     return wrong;
+}
+
+// The route of a launch over n members, bit i of f16 the route of member i.
+int pc_route(int n, unsigned f16) {
+    qlin_s h[kMaxMembers];
+    Target t;
+    t.nmem = n;
+    for (int i = 0; i < n; ++i) {
+        h[i].f16 = (f16 >> i) & 1u;
+        t.mem[i] = &h[i];
+    }
+    return route_of(t);
 }
 
 // Most 16-byte units on one LDS bank group (of 16) among 16 lanes in a row, for

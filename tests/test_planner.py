@@ -109,3 +109,12 @@ def test_partial_sums_in_lds_spread_over_the_banks(planner):
     """The 16-byte writes and reads of the partial sums by 16 neighbouring lanes
     touch every bank once (in row order the writes would meet four to a bank)."""
     assert planner.pc_sums_conflicts(144) == 1
+
+
+def test_members_of_one_route_take_its_kernel(planner):
+    """Only a group of both routes (2) runs the kernels that hold both."""
+    for n in (1, 2, 8):
+        every = (1 << n) - 1
+        assert [planner.pc_route(n, m) for m in (0, every)] == [0, 1]
+        for mixed in {1, every >> 1, every & ~1} - {0, every}:
+            assert planner.pc_route(n, mixed) == 2
