@@ -8,6 +8,23 @@
 
 namespace qlin {
 
+// The direct-to-LDS loads of x: rows of 128 k, or of 64 (HALF), 1 KiB a load.
+template <bool HALF>
+struct XLoads {
+    static constexpr int kChunks = HALF ? 8 : 16, kRows = 64 / kChunks, kLoads = 16 / kRows;
+    uint32_t at[kLoads], last[kLoads];        // byte offsets of this lane's chunk; in the last m-tile
+    __device__ static inline int swizzle(int row, int c) { return HALF ? c ^ ((row >> 1) & 7) : c ^ (row & 15); }
+    __device__ inline XLoads(int lane, uint32_t row_bytes, int last_row) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int r = kRows * i + lane / kChunks;
+            const uint32_t c = (uint32_t)swizzle(r, lane % kChunks) * 16u;
+            at[i] = (uint32_t)r * row_bytes + c;
+            last[i] = (uint32_t)min(r, last_row) * row_bytes + c;
+        }
+    }
+};
+
 // A workgroup owns K chunk c (groups [g0, g0 + Kc)) of column tiles
 // [t0, t0 + Tn), Tn <= TN, and all 16 MT rows: every weight of the launch is
 // read and dequantized exactly once.  Its 8 waves cut the K range: in a round
@@ -17,8 +34,9 @@ namespace qlin {
 // and LDS bandwidth would bound the kernel from 32 rows on.  A unit is a group
 // (128 k) up to 64 rows and half a group beyond, where the x of a whole one
 // would take 32 MT of a lane's registers.  With whole groups a last round of
-// up to four gives each to two waves: every other tile each, or, of one tile,
-// 64 k each.
+// up to four gives each to two waves, 64 k each; with at most one round before it
+// they load no more than they use: every other tile each where it is the only
+// round, or, of one tile, 64 k.
 //
 // The waves share nothing before the end: a wave stages its unit's x in LDS
 // of its own with direct-to-LDS loads (LDS only turns rows into operand
@@ -42,13 +60,13 @@ namespace qlin {
 // 13.3 / 15.4 (17.1 / 17.1), 512 x 2048 at 65 / 128 rows 4.3 / 5.2 (5.7 / 5.9).
 //
 // At the end the waves' sums are added in LDS in a fixed order: wave w + 4 to
-// wave w, then the four sums in order; of a single round of shared groups each
-// pair of waves is one of the four.  LDS bandwidth bounds this end, 16 KB a tile
-// and m-tile: with sums in row order (four lanes to a bank), every wave's sums of
-// every tile and both waves of a pair loading all of a shared group's weights,
-// 512 x 19456 at 17 / 48 rows took 6.6 / 7.8 us, now 5.7 / 6.6 (1024 x 19456
-// 7.5 / 9.0, now 7.1 / 8.3).  The last round is code of its own: tests of a round's kind
-// in front of each tile's loads cost the whole rounds 0.4 us.
+// wave w, then the four sums in order; of a single round of groups shared by tile
+// each pair of waves is one of the four.  LDS bandwidth bounds this end, 16 KB a
+// tile and m-tile.  With sums in row order (four lanes to a bank), every wave's
+// sums of every tile, and both waves of a pair loading all of a shared group,
+// 512 x 19456 at 17 / 48 / 64 rows took 6.6 / 7.8 / 8.3 us, now 5.5 / 6.4 / 7.0,
+// 512 x 4096 at 64 rows 5.2, now 4.8.  Longer walks are one loop: a last round as
+// code of its own behind it takes 9.3 us for 2560 x 12288 at 17 rows, not 8.3.
 //
 // x of a wave in LDS: 16-byte chunk c (k = 8 c) of row r at slot
 // 16 r + (c ^ (r & 15)), as in the tiled kernel, or, with half-group units,
@@ -73,35 +91,37 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     const int full = units / kWaves, rem = units % kWaves;
     const bool paired = !HG && rem <= kHalf;
     const int tail = paired ? wave >> 1 : wave;      // its unit among the last ones
-    const bool last = tail < rem;                    // takes part in the last round
+    const int last = tail < rem ? 1 : 0;             // takes part in the last round
+    const bool alone = paired && full == 0;          // one round of shared groups is all
     auto other = [&](int t) { return ((t ^ wave) & 1) != 0; };   // a tile of the other wave of its pair
     auto group_of = [&](int u) { return HG ? u >> 1 : u; };
     auto half_of = [&](int u) { return HG ? (uint32_t)(u & 1) : 0u; };
 
-    // x: load (mt, i) fills rows 16 mt + kRowsLoad i + lane / kChunks; rows >= M
-    // (only in the last m-tile) are copies of row M - 1 and feed no stored output
-    constexpr int kChunks = HG ? 8 : 16, kRowsLoad = 64 / kChunks, kLoads = 16 / kRowsLoad;
+    // what a wave loads for a round: its unit, every other tile of a shared group
+    // (and its x), or 64 k of one
+    enum Share { kWhole, kTiles, kHalves };
+    // x of a unit (or, in half-group rows, of a half): load (mt, i) fills rows
+    // 16 mt + kRows i + lane / kChunks; rows >= M (only in the last m-tile) are
+    // copies of row M - 1 and feed no stored output
     const uint32_t row_bytes = (uint32_t)a.K * 2u;
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, (int)((uint32_t)a.M * row_bytes), kRsrcFlags);
-    auto swizzle = [&](int row, int c) { return HG ? c ^ ((row >> 1) & 7) : c ^ (row & 15); };
-    uint32_t xv[kLoads], xl[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-        const int r = kRowsLoad * i + lane / kChunks;
-        const uint32_t c = (uint32_t)swizzle(r, lane % kChunks) * 16u;
-        xv[i] = (uint32_t)r * row_bytes + c;
-        xl[i] = (uint32_t)min(r, a.M - 1 - 16 * (MT - 1)) * row_bytes + c;
-    }
     const uint32_t lds_x = lds_addr(smem) + wave * kWaveX;
-    auto load_x = [&](int u) {
-        const uint32_t off = (uint32_t)(w.g0 + group_of(u)) * 256u + half_of(u) * 128u;
+    const XLoads<HG> xl(lane, row_bytes, a.M - 1 - 16 * (MT - 1));
+    const XLoads<true> xh(lane, row_bytes, a.M - 1 - 16 * (MT - 1));   // unused but for kHalves
+    auto load_x = [&](auto share, int u) {
+        constexpr bool kHalf64 = share == kHalves;
+        const auto &x = [&]() -> const auto & {
+            if constexpr (kHalf64) return xh;
+            else return xl;
+        }();
+        const uint32_t off = (uint32_t)(w.g0 + group_of(u)) * 256u + (kHalf64 ? wave & 1 : half_of(u)) * 128u;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < kLoads; ++i)
-                load_lds_buf16(rx, mt == MT - 1 ? xl[i] : xv[i], off + mt * 16 * row_bytes,
-                               lds_x + (mt * kLoads + i) * 1024u);
+            for (int i = 0; i < x.kLoads; ++i)
+                load_lds_buf16(rx, mt == MT - 1 ? x.last[i] : x.at[i], off + mt * 16 * row_bytes,
+                               lds_x + (mt * x.kLoads + i) * 1024u);
     };
     // weights and scales of group kb; lane (lg, lm) of scale load i holds column lm of tile 4 i + lg
     const size_t base = (size_t)w.t0 * a.Kb + w.g0;
@@ -119,7 +139,6 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         words_t c[TN];
         uint32_t s[NS];
     };
-    enum Share { kWhole, kTiles, kHalves };          // a round's part of this wave: its unit, or of a shared one
     auto load_w = [&](auto share, Unit &g, int u) {
         const int kb = group_of(u);
 #pragma unroll
@@ -128,10 +147,15 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         for (int t = 0; t < TN; ++t) {
             if (share == kTiles && other(t)) continue;
             const uint32_t soff = (uint32_t)(min(t, w.Tn - 1) * a.Kb + kb) * 1024u;
-            if constexpr (HG)
+            if constexpr (HG) {
                 g.c[t] = __builtin_amdgcn_raw_buffer_load_b64(rc, lane * 16 + half_of(u) * 8, soff, kWeightPolicy);
-            else
+            } else if constexpr (share == kHalves) {
+                const v2u c = __builtin_amdgcn_raw_buffer_load_b64(rc, lane * 16 + (wave & 1) * 8, soff, kWeightPolicy);
+                g.c[t][0] = c[0];
+                g.c[t][1] = c[1];
+            } else {
                 g.c[t] = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 16, soff, kWeightPolicy);
+            }
         }
     };
     v4f acc[TN][MT];
@@ -139,7 +163,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     for (int t = 0; t < TN; ++t)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[t][mt] = v4f{0, 0, 0, 0};
-    const uint4 *xb = (const uint4 *)(smem + wave * kWaveX) + lm * kChunks;
+    const uint4 *xs = (const uint4 *)(smem + wave * kWaveX);
 
     auto walk = [&](auto route) {
         constexpr bool F16 = decltype(route)::value;
@@ -147,19 +171,22 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
         const DeqSel<SYM, F16> dsel(lane);
         Unit g;
         auto request = [&](auto share, int u) {
-            load_x(u);
+            load_x(share, u);
             load_w(share, g, u);
         };
-        // one round on what is in flight; `next` requests the round after it
-        auto round = [&](auto share, auto next) {
+        // one round on what is in flight; `next` requests the round after it.  Of
+        // a whole unit the wave takes its first 64 k, its second or both
+        auto round = [&](auto share, auto next, bool lo, bool hi) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this round's x is in LDS
             const Unit cur = g;
-            v8bf xf[KJ][MT];
+            constexpr int kSteps = share == kHalves ? 2 : KJ;
+            using X = XLoads<HG || share == kHalves>;
+            v8bf xf[kSteps][MT];
 #pragma unroll
-            for (int j = 0; j < KJ; ++j)
+            for (int j = 0; j < kSteps; ++j)
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    xf[j][mt] = __builtin_bit_cast(v8bf, xb[mt * 16 * kChunks + swizzle(lm, 4 * j + lg)]);
+                    xf[j][mt] = __builtin_bit_cast(v8bf, xs[(16 * mt + lm) * X::kChunks + X::swizzle(lm, 4 * j + lg)]);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // and in registers: its LDS is free
             next();
             uint32_t sz[4 * NS];
@@ -178,37 +205,54 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
                 if (t >= w.Tn || (share == kTiles && other(t))) continue;
                 const MfmaDeq d = dsel.setup(sz[t]);
 #pragma unroll
-                for (int j = 0; j < KJ; ++j) {
-                    if (share == kHalves && (j >> 1) != (wave & 1)) continue;
-                    const v8bf wa = mfma_dequant<F16>(cur.c[t][j], d, kx);
+                for (int jj = 0; jj < kSteps; jj += 2) {
+                    if (share == kWhole && !HG && !(jj ? hi : lo)) continue;
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-                        acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[j][mt], acc[t][mt], 0, 0, 0);
+                    for (int j = jj; j < jj + 2; ++j) {
+                        const v8bf wa = mfma_dequant<F16>(cur.c[t][j], d, kx);
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt)
+                            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, xf[j][mt], acc[t][mt], 0, 0, 0);
+                    }
                 }
             }
         };
         using Whole = std::integral_constant<Share, kWhole>;
         using Part = std::integral_constant<Share, kShareTiles ? kTiles : kHalves>;
-        auto request_last = [&] {
-            if (!last) return;
-            if (paired) request(Part{}, full * kWaves + tail);
-            else request(Whole{}, full * kWaves + tail);
-        };
-        if (full > 0) {
-            request(Whole{}, wave);
-            for (int r = 1; r < full; ++r) round(Whole{}, [&] { request(Whole{}, r * kWaves + wave); });
-            round(Whole{}, request_last);
-        } else {
-            request_last();
+        if constexpr (kShareTiles) {
+            if (alone) {
+                request(Part{}, tail);
+                round(Part{}, [] {}, true, true);
+                return;
+            }
+        } else if constexpr (!HG) {
+            if (full < 2) {
+                auto request_last = [&] {
+                    if (last && paired) request(Part{}, full * kWaves + tail);
+                    else if (last) request(Whole{}, full * kWaves + tail);
+                };
+                if (full == 1) {
+                    request(Whole{}, wave);
+                    round(Whole{}, request_last, true, true);
+                } else {
+                    request_last();
+                }
+                if (last && paired) round(Part{}, [] {}, true, true);
+                else if (last) round(Whole{}, [] {}, true, true);
+                return;
+            }
         }
-        if (last) {
-            if (paired) round(Part{}, [] {});
-            else round(Whole{}, [] {});
+        auto unit_of = [&](int r) { return r < full ? r * kWaves + wave : full * kWaves + tail; };
+        request(Whole{}, unit_of(0));
+        for (int r = 0; r < full + last; ++r) {
+            const bool whole = r < full || !paired;
+            round(Whole{}, [&] { if (r + 1 < full + last) request(Whole{}, unit_of(r + 1)); },
+                  whole || (wave & 1) == 0, whole || (wave & 1) == 1);
         }
     };
     // Both routes in one kernel: with a route each the compiler copies the sums
-    // between registers from round to round (1024 x 19456 at 17 rows 7.5 us, not 7.0).
-    if (full > 0 || last) on_route<kRouteMixed>(w.f16, walk);
+    // between registers from round to round (1024 x 19456 at 17 rows 7.5 us, not 7.1).
+    if (full + last > 0) on_route<kRouteMixed>(w.f16, walk);
 
     // sums: [set < 4][tile][row][16 columns] fp32 in LDS, over the x, in the order
     // of sums_unit().  D of the 16x16 op: lane l holds columns 4 (l >> 4) + v of row l & 15
@@ -217,7 +261,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     auto at = [&](int set, int t, int mt) {
         return (v4f *)(sums + (size_t)(set * TN + t) * ROWS * 16 + 4 * sums_unit(16 * mt + lm, lg));
     };
-    if (kShareTiles && paired && full == 0) {
+    if (kShareTiles && alone) {
         // one round of shared groups: the pairs are the sets, each tile in one wave of a pair
 #pragma unroll
         for (int t = 0; t < TN; ++t)
