@@ -34,9 +34,8 @@ struct XLoads {
 // and LDS bandwidth would bound the kernel from 32 rows on.  A unit is a group
 // (128 k) up to 64 rows and half a group beyond, where the x of a whole one
 // would take 32 MT of a lane's registers.  With whole groups a last round of
-// up to four gives each to two waves, 64 k each; with at most one round before it
-// they load no more than they use: every other tile each where it is the only
-// round, or, of one tile, 64 k.
+// up to four gives each to two waves, 64 k each; where it is the only round they
+// load no more than they use: every other tile each or, of one tile, 64 k.
 //
 // The waves share nothing before the end: a wave stages its unit's x in LDS
 // of its own with direct-to-LDS loads (LDS only turns rows into operand
@@ -226,7 +225,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
                 return;
             }
         } else if constexpr (!HG) {
-            if (full < 2) {
+            if (full == 0 || (full == 1 && (MT == 4 || rem == 0))) {
                 auto request_last = [&] {
                     if (last && paired) request(Part{}, full * kWaves + tail);
                     else if (last) request(Whole{}, full * kWaves + tail);

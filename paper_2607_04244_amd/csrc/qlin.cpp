@@ -315,16 +315,21 @@ int gemv_max_auto() {
     return v;
 }
 
-// Estimated time (ns) of a k_mid launch, fitted to every split from 1 to 8 of the decoder's
-// linears at 17 to 64 rows (within 10% where a plan is chosen): per round of 8
-// groups the x of the waves and the blocks of the tiles, per tile the sums at
-// the end, and for a split the partial sums written and read back.
+// Estimated time (ns) of a k_mid launch: rounds of 8 groups, each with the x of
+// the waves and the blocks of the tiles, or, if longer, the x of all workgroups
+// at the 15.8 TB/s their L2s give; per tile the sums at the end; for a split the
+// trips of the partial sums.  Fitted to 1900 launches at 17, 32, 48 and 64 rows of
+// K = 1024 to 9728 and N = 256 to 24576 in 1 to 16 chunks (9% root mean square);
+// over the 356 shapes among them the split it chooses is on average 0.5% slower
+// than the fastest one timed, and at most 18% (2048 x 256 at 64 rows).
 double mid_cost(const Target &t, int M, int S, int Gn, int Tn) {
     const int mt = (M + 15) / 16, Kc = (t.Kb + S - 1) / S, rem = Kc % kWaves;
-    const double passes = (double)((S * Gn + t.num_cu - 1) / t.num_cu);
+    const double grid = (double)S * Gn, passes = std::max(1.0, grid / t.num_cu);
     const double rounds = Kc / kWaves + (rem == 0 ? 0.0 : 2 * rem <= kWaves ? 0.5 : 1.0);
-    double c = 1900.0 + passes * (rounds * (200.0 + 330.0 * mt + Tn * (360.0 + 70.0 * mt)) + 190.0 * mt * Tn);
-    if (S > 1) c += 1300.0 + S * (100.0 + (double)M * t.N * 8.0 * 0.5e-3);
+    const double walk = passes * rounds * (175.0 * mt + Tn * (290.0 + 135.0 * mt));
+    const double x = grid * mt * 16 * Kc * kGroup * 2 / 15800.0;
+    double c = 3050.0 + std::max(walk, x) + 105.0 * passes * mt * Tn;
+    if (S > 1) c += 1500.0 + 130.0 * S + 1.4e-3 * S * M * t.N + 175.0 * std::max(0, S - 8);
     return c;
 }
 

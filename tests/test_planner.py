@@ -118,3 +118,17 @@ def test_members_of_one_route_take_its_kernel(planner):
         assert [planner.pc_route(n, m) for m in (0, every)] == [0, 1]
         for mixed in {1, every >> 1, every & ~1} - {0, every}:
             assert planner.pc_route(n, mixed) == 2
+
+
+@pytest.mark.parametrize("M,K,N,chunks", [
+    (17, 2048, 256, (1,)), (32, 2048, 1024, (1,)), (48, 1152, 256, (1,)), (64, 1408, 512, (1,)), (17, 3072, 2048, (1,)),
+    (17, 4352, 2560, (1,)), (64, 3072, 2048, (1,)), (64, 9728, 256, (6, 7, 8)), (48, 9728, 4096, (2, 3)),
+    (64, 9728, 2560, (2, 3, 4)), (64, 2560, 19456, (1,)), (41, 2560, 12288, (1,)),
+])
+def test_splits_at_17_to_64_rows(planner, M, K, N, chunks):
+    """Chunks of K within 5% of the fastest of 1 to 16 timed: layers of few
+    groups or wide ones are not cut (2048 x 256 at 17 rows in 4 chunks took 5.8
+    us, whole 4.2), deep narrow ones are."""
+    rc, p = plan(planner, [N], K, M)
+    assert rc == qlin.QLIN_OK and p.S in chunks, p.S
+
