@@ -634,25 +634,33 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
 
 // k_mid beyond 64 rows (up to 144, without a K split), where it is estimated
 // faster than the tiled plan q the workspace allows.  Both estimates (us) are
-// fitted to 65 .. 144 rows of K = 512 .. 9728, N = 2048 .. 19456: per group of
-// K, k_mid pays for its m-tiles and tiles, the 64 x 128 blocks of the tiled
-// kernel 0.63 us (1.5 times that with two blocks a compute unit), the taller
-// ones 2 us, and a K split its partial blocks; of the 117 shapes timed there,
-// none came out more than 3 % slower than its tiled plan.  Measured, k_mid against the
-// tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows 10.9 / 12.8 / 15.4 us against
-// 14.1 / 14.1 / 17.0, 4096 x 6144 14.1 / 16.6 / 21.0 against 17.7 / 17.8 / 23.6;
-// at 112 rows both take 14.1 and past 144 rows x no longer fits LDS.
+// fitted to 2180 launches at 65 .. 144 rows of K = 512 .. 12800, N = 208 ..
+// 12288, with and without a workspace (k_mid 5%, tiled 3% root mean square): k_mid
+// pays per group for its m-tiles and tiles or, if longer, for the x of all
+// workgroups at 18.2 TB/s; the tiled kernel per group of K for a 64 x 128 block,
+// half of one more for each further round of blocks, or for a taller one, and for
+// a K split its chunks and partial blocks.  Of 1320 choices timed there one came
+// out more than 3 % slower than the tiled plan (5 %) and 987 faster; on average a
+// choice is 0.1 % slower than the better kernel.  Measured, k_mid against the
+// tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows 10.8 / 12.9 / 15.4 us against
+// 14.3 / 14.4 / 17.3, 640 x 208 at 144 rows 5.0 against 6.0; 9728 x 3872 at 144
+// rows 38.6 against 30.7, 2944 x 2560 at 144 rows 14.4 against 12.1 (both tiled);
+// past 144 rows x no longer fits LDS.
 bool make_mid_plan(const Target &t, int64_t M, const Plan &q, Plan *p) {
     const int mt = (int)((M + 15) / 16);
     if (mt > kMidTilesM) return false;
     const int Gn = std::min(t.Nt, t.num_cu), Tn = ranges_tnmax(t, Gn);
     if (Tn < 1 || Tn > mid_tiles_max(mt) || (int64_t)Tn * t.Kb * 1024 >= ((int64_t)1 << 31)) return false;
-    const double mid = 4.5 + t.Kb * (0.13 + 0.046 * mt + 0.024 * mt * (Tn - 2));
-    const int64_t blocks = (int64_t)q.Gn * ((M + q.mrows - 1) / q.mrows);
-    const double load = (double)((blocks * q.S + t.num_cu - 1) / t.num_cu);
-    const double group = q.tn == 2 ? 0.63 * (0.5 + 0.5 * load) : 2.0 * load;
-    double tiled = 4.0 + group * ((t.Kb + q.S - 1) / q.S);
-    if (q.S > 1) tiled += 1.0 + 2.0 * (double)q.floats * 4.0 / 4.0e6;
+    const double tiles = 0.55 * Tn + 0.45 * t.Nt / Gn;            // between the widest range and the average
+    const double walk = 0.25 * t.Kb * (0.225 + mt * (0.113 + 0.045 * Gn / t.num_cu) + tiles * (0.198 + 0.0146 * mt));
+    const double x_mb = (double)Gn * mt * 16 * t.Kb * kGroup * 2 * 1e-6;
+    const double mid = 2.17 + std::max(walk, x_mb / 18.2) + 0.165 * mt * tiles;
+    const double work = (double)q.Gn * ((M + q.mrows - 1) / q.mrows) * q.S;      // blocks times chunks
+    const double load = std::ceil(work / t.num_cu), Kc = (t.Kb + q.S - 1) / q.S;
+    double tiled = 3.74;
+    if (q.tn == 2) tiled += Kc * (0.592 + 0.306 * (load - 1.0) + 0.148 * std::min(1.0, work / t.num_cu));
+    else tiled += 6.47 + Kc * load * (q.mrows == 128 ? 1.96 : 1.26);
+    if (q.S > 1) tiled += 0.92 + 0.456 * q.S + 0.22 * (double)q.floats * 4e-6;
     if (mid >= 0.97 * tiled) return false;
     *p = Plan();
     p->path = kTiled;

@@ -132,3 +132,18 @@ def test_splits_at_17_to_64_rows(planner, M, K, N, chunks):
     rc, p = plan(planner, [N], K, M)
     assert rc == qlin.QLIN_OK and p.S in chunks, p.S
 
+
+TILED_KERNEL, MID_KERNEL = 3, 4
+
+
+@pytest.mark.parametrize("M,K,N,ws,kern", [
+    (144, 9728, 3872, -1, TILED_KERNEL), (144, 2944, 2560, -1, TILED_KERNEL), (128, 2944, 3872, -1, TILED_KERNEL),
+    (97, 4096, 3872, -1, TILED_KERNEL), (96, 9728, 8192, -1, TILED_KERNEL), (128, 4096, 2560, -1, TILED_KERNEL),
+    (145, 512, 2048, -1, TILED_KERNEL), (65, 2560, 6144, -1, MID_KERNEL), (129, 2560, 6144, -1, MID_KERNEL),
+    (65, 1792, 256, -1, MID_KERNEL), (96, 2560, 12288, 0, MID_KERNEL), (144, 9728, 2560, 0, MID_KERNEL),
+])
+def test_kernel_at_65_to_144_rows(planner, M, K, N, ws, kern):
+    """The faster kernel where both were timed and differ by 8% and more (9728 x
+    3872 at 144 rows: 38.6 us in k_mid, 30.7 as eight K chunks of the tiled one)."""
+    rc, p = plan(planner, [N], K, M, ws=ws)
+    assert rc == qlin.QLIN_OK and p.kern == kern, p.kern
