@@ -17,6 +17,7 @@ using namespace qlin;
 namespace {
 
 constexpr int64_t kMaxT = (int64_t)1 << 28;
+constexpr int kMaxSharedRange = 24, kMaxSharedWhole = 64;     // 64-key tiles: see make_attn_plan
 
 struct AttnPlan {
     int G = 1, half = -1, lo = 0, hi = 0, ntiles = 0, tps = 1, S = 1;
@@ -48,7 +49,6 @@ int make_attn_plan(int64_t Hq, int64_t Hkv, int64_t nq, int64_t T, int64_t windo
     p->ntiles = (p->hi - p->lo + kAttnTile - 1) / kAttnTile;
     int64_t S = splits;
     int cus = 0;
-    const bool spread = S == 0;
     if (S == 0) {
         int dev = 0;
         hipError_t e = hipGetDevice(&dev);
@@ -65,17 +65,33 @@ int make_attn_plan(int64_t Hq, int64_t Hkv, int64_t nq, int64_t T, int64_t windo
         const int keys = p->hi - p->lo;
         p->block = keys <= (p->G > kAttnWaves ? kAttnBlockUnits : kAttnBlockUnits - 2) * kAttnUnit &&
                    Hq * (kAttnD / kAttnSlice) <= cus;
-        // More than four query heads: two workgroups a (head, range), one head
-        // a wave, over ranges twice as long, rather than two heads in turn in
-        // each wave: measured 9.4 -> 7.8 us (64 / 8 heads, 528 keys), 20.0 ->
-        // 18.5 (8192 keys), 25.8 -> 18.3 (8 / 1 heads, 16000 keys), 11.5 ->
-        // 10.7 (24 / 4 heads, 1500 keys); none of 17 shapes was slower.
-        S = p->block ? 1 : std::max<int64_t>(1, cus / (Hkv * (p->G > kAttnWaves ? 2 : 1)));
+        S = p->block ? 1 : std::max<int64_t>(1, cus / Hkv);
     }
-    S = std::min<int64_t>({S, (int64_t)p->ntiles, (int64_t)kAttnMaxSplits});
-    p->tps = (int)((p->ntiles + S - 1) / S);
-    p->S = (p->ntiles + p->tps - 1) / p->tps;
-    if (spread && p->G > kAttnWaves && 2 * Hkv * p->S <= cus) p->ng = 2;
+    auto cut = [&](int64_t n) {
+        n = std::min<int64_t>({n, (int64_t)p->ntiles, (int64_t)kAttnMaxSplits});
+        p->tps = (int)((p->ntiles + n - 1) / n);
+        p->S = (p->ntiles + p->tps - 1) / p->tps;
+    };
+    cut(S);
+    // More than four query heads: two workgroups a (head, range), one head a
+    // wave, over ranges twice as long, rather than two heads in turn in each wave:
+    // measured 9.4 -> 7.8 us (64 / 8 heads, 528 keys), 20.0 -> 18.5 (8192 keys),
+    // 25.8 -> 18.3 (8 / 1 heads, 16000 keys), 24.8 -> 17.3 (520 / 65 heads, 700
+    // keys, one range and no combination).  Not where whole numbers of ranges make
+    // them longer than that (520 / 65 heads, 2064 keys, one range for three: 36.7
+    // -> 40.1), nor for long ones, which gain nothing from it (120 / 24 heads, 8192
+    // keys, 26 tiles a range: 34.1 -> 35.3; 320 / 64 heads, 64 tiles: 71 -> 76)
+    // but for the combination where one range is left and both workgroups share an
+    // L2 (768 / 96 heads, 33 and 64 tiles: 48 -> 39.5, 74 -> 69; 1016 / 127 heads,
+    // whose pairs sit on two XCDs: 55 -> 64).
+    if (splits == 0 && !p->block && p->G > kAttnWaves && 2 * Hkv <= cus) {
+        const int one = p->tps;
+        cut(std::max<int64_t>(1, cus / (2 * Hkv)));
+        const bool brief = p->tps <= kMaxSharedRange;
+        if (p->tps <= 2 * one + 1 ? brief || (p->S == 1 && p->tps <= kMaxSharedWhole && Hkv % 8 == 0)
+                                  : brief && p->S == 1) p->ng = 2;
+        else cut(S);
+    }
     // partials of every (head, split) cover all 16 rows of the query tile
     p->ws_bytes = p->S > 1 ? (int64_t)p->S * Hq * kAttnQ * (kAttnD + 2) * 4 : 0;
     return QLIN_OK;
