@@ -66,7 +66,11 @@ __device__ inline float bf16_hi_to_f32(uint32_t w) { return __uint_as_float(w & 
 // r >= 2 of a 4-column block, whose codes sit at bits 4-7.  All weights then
 // come out multiplied by 2^(kF16Exp - 24), exactly, so they round to the same
 // bf16 significands, and the sum is multiplied by kF16Unscale before its one
-// rounding.
+// rounding.  The matrix cores keep binary32's subnormals, so sums stay as exact
+// as on the other route while products x w are above 2^-114; below, they are
+// multiples of 2^-137 (not 2^-149), 1/16 of the smallest bf16 step: outputs in
+// bf16's own subnormal range, below 2^-126, may be off by a step more (measured at
+// 2^-128: relative error 7.2e-3 against 5.8e-3; from 2^-124 up no difference).
 //
 // F16 = false (any scale in [2^-100, 2^100]): 0x4300 | q is the bf16 number
 // 128 + q: three shifts and four v_and_or_b32 per word.
@@ -262,14 +266,15 @@ __device__ inline ValuDeq valu_setup(const uint32_t sz[4]) {
 
 // The bf16 word s | zc << 16 of column r of a 4-column block from what a
 // handle stores for it (v = the 32-bit word, or for symmetric handles the 16
-// bits in the half of the column's parity).  For f16 = true the scale comes
-// out as s 2^(kF16Exp - 24): the weights have the scaling of the matrix-core
-// route.
+// bits in the half of the column's parity).  The scale comes out itself, whatever
+// the route: the vector unit flushes binary32's subnormals, so scaled sums would
+// vanish 2^12 earlier.
 template <bool SYM>
 __device__ inline uint32_t valu_word(uint32_t v, int r, bool f16) {
     const uint32_t own = (r & 1) ? v >> 16 : v & 0xFFFFu, other = (r & 1) ? v & 0xFFFFu : v >> 16;
     if (f16) {
-        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)own) * (r >= 2 ? 0x1p-20f : 0x1p-24f);
+        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)own) *
+                        __builtin_ldexpf(1.0f, r >= 2 ? 4 - kF16Exp : -kF16Exp);
         const uint32_t z = SYM ? 8u : (other & 0x7FFFu) >> (r >= 2 ? 4 : 0);
         return (__float_as_uint(s) >> 16) | ((0xC300u | z) << 16);
     }

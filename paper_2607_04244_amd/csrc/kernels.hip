@@ -112,8 +112,8 @@ __global__ void k_unpack(const uint4 *__restrict__ codes, uint8_t *__restrict__ 
     }
 }
 
-// Both dequantizing hooks undo the F16 route's power-of-two scaling (exactly)
-// before they store.
+// This dequantizing hook undoes the F16 route's power-of-two scaling (exactly)
+// before it stores.
 template <bool SYM, bool F16>
 __global__ void k_dequant_mfma(const uint4 *__restrict__ codes, const void *__restrict__ sz,
                                uint16_t *__restrict__ w, int K, int N) {
@@ -150,7 +150,6 @@ __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__re
     const int l = threadIdx.x & 63;
     const int b2 = (l >> 2) & 3;
     const ExtractConsts<false> kx;
-    const float unscale = f16 ? kF16Unscale : 1.0f;
     for (size_t b = (size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nblocks;
          b += (size_t)gridDim.x * (blockDim.x >> 6)) {
         const uint4 c = codes[b * 64 + l];
@@ -165,8 +164,8 @@ __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__re
             for (int r = 0; r < 4; ++r) {
                 const size_t n = (size_t)t * kTileN + 4 * b2 + r;
                 const int k0 = kb * kGroup + 32 * j + 8 * (l >> 4) + (l & 3);
-                w[n * K + k0] = (uint16_t)(__float_as_uint(bf16_lo_to_f32(pr[r]) * unscale) >> 16);
-                w[n * K + k0 + 4] = (uint16_t)(__float_as_uint(bf16_hi_to_f32(pr[r]) * unscale) >> 16);
+                w[n * K + k0] = (uint16_t)(pr[r] & 0xFFFFu);
+                w[n * K + k0 + 4] = (uint16_t)(pr[r] >> 16);
             }
         }
     }
@@ -493,7 +492,8 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ExtractConsts<false> kx;
-    const WgWork w = wg_work<R>(a, blockIdx.x);
+    WgWork w = wg_work<R>(a, blockIdx.x);
+    w.unscale = 1.0f;                              // valu_word() does not scale
     const int Tn = w.Tn;
     int u0, u1;
     wave_range(Tn * w.Kc, wave, u0, u1);

