@@ -4,11 +4,13 @@ an MI355X), against the float64 oracle within the tolerance derived in
 test_attn: the edges of the 32-key units and of the rules.
 """
 
+import numpy as np
 import pytest
 import torch
 
+from oracle import attn_ref as ar
 from paper_2607_04244_amd import qlin
-from test_attn import case, check
+from test_attn import case, check, host_f64, run, tolerance
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +80,22 @@ def test_when_two_workgroups_share_a_head(Hq, Hkv, T, kernel, splits):
         q, k, v = case(Hq, Hkv, 2, T, seed=T)
         check(q, k, v, T, 0, what=f"{Hq}/{Hkv} T={T}")
 
+
+@pytest.mark.parametrize("T", [100, 300, 700])
+def test_infinite_keys_and_values(T):
+    """A key of -infinity under positive queries has weight zero, and an
+    infinite value stays in its dimension (infinite, or NaN where its weight is
+    zero in bf16), in one kernel and in the split."""
+    Hq, Hkv, nq = 8, 2, 16
+    q, k, v = case(Hq, Hkv, nq, T, seed=T)
+    q = np.maximum(q & 0x7FFF, 0x3C00).astype(np.uint16)            # positive
+    k[:, 7] = 0xC640                                                # -12288: the weight vanishes as well
+    ref = ar.swa_attention(q, k[:, :T], v[:, :T], 0)
+    k[:, 7] = 0                                                     # a key without weight adds no error
+    tol = tolerance(q, k, v, T, 0, ref)
+    k[:, 7] = 0xFF80
+    v[:, 50, 3] = 0x7F80
+    got = host_f64(run(q, k, v, T, 0))
+    rest = np.arange(128) != 3
+    assert np.all(np.abs(got - ref)[..., rest] <= tol[..., rest])
+    assert not np.isfinite(got[..., 3]).any() and not np.isneginf(got[..., 3]).any()

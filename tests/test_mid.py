@@ -177,3 +177,22 @@ def test_vector_kernel_has_one_range_on_both_routes(sym):
     f16.close()
     bf16.close()
 
+
+@pytest.mark.parametrize("path,M", PATHS + [(AUTO, 64), (AUTO, 80)])
+def test_infinities_and_nans_stay_in_their_rows(path, M):
+    """An infinity and a NaN in two rows of x: those rows' outputs are infinite
+    or NaN where the exact sums are, the others keep their bits."""
+    c = gen.random_case(31, M, 640, 272)
+    lin = make(c)
+    clean = run(lin, c["x"], path)
+    x = c["x"].copy()
+    rows = [0, M - 1]
+    x[0, 130], x[M - 1, 5] = 0x7F80, 0x7FC0
+    y = run(lin, x, path)
+    assert np.array_equal(np.delete(y, rows, axis=0), np.delete(clean, rows, axis=0))
+    w = ref.bf16_to_f64(ref.dequant_bf16(c["packed"], c["scales"], c["zeros"]))
+    got = ref.bf16_to_f64(y)
+    assert np.all(np.isnan(got[M - 1]))
+    zero = w[:, 130] == 0
+    assert np.all(np.isnan(got[0, zero])) and np.array_equal(got[0, ~zero], np.sign(w[~zero, 130]) * np.inf)
+    lin.close()
