@@ -68,7 +68,7 @@ def algorithmic_bytes(M, K, N, symmetric=False):
 KERNEL_SOURCES = {
     "linear": ("kernels.hip", "decode_common.h", "device_common.h", "qlin_internal.h"),
     "mid": ("mid.hip", "decode_common.h", "device_common.h", "qlin_internal.h"),
-    "tiled": ("tiled.hip", "device_common.h", "qlin_internal.h"),
+    "tiled": ("tiled.hip", "decode_common.h", "device_common.h", "qlin_internal.h"),
     "attention": ("attn.hip", "attn_internal.h", "device_common.h", "qlin_internal.h"),
 }
 

@@ -249,36 +249,41 @@ __device__ inline v8bf mfma_dequant(uint32_t P, const MfmaDeq &d, const ExtractC
 
 // --- vector-ALU dequantization -------------------------------------------
 
-// Constants for the four columns n = 16 t + 4 * ((l >> 2) & 3) + r of lane l,
-// from words s | zc << 16 in bf16 (the F16 = false form).
+// Constants for the four columns n = 16 t + 4 * ((l >> 2) & 3) + r of lane l.
+// The scales are the weights' own on either route: the vector unit flushes
+// binary32's subnormals, so scaled sums would vanish 2^12 earlier.
 struct ValuDeq { uint32_t sl[4], sh[4]; float c[4]; };
 
-__device__ inline ValuDeq valu_setup(const uint32_t sz[4]) {
+// v[r]: what a handle stores for column r (the 32-bit word, or for symmetric
+// handles the 16 bits in the half of the column's parity).
+template <bool SYM>
+__device__ inline ValuDeq valu_setup(const uint32_t v[4], bool f16) {
     ValuDeq d;
+    if (f16) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint16_t own = (uint16_t)((r & 1) ? v[r] >> 16 : v[r]);
+            const float s = (float)__builtin_bit_cast(_Float16, own) * __builtin_ldexpf(1.0f, r >= 2 ? 4 - kF16Exp : -kF16Exp);
+            d.sh[r] = __float_as_uint(s);          // 8 significant bits: the bf16 pair (0, s)
+            d.sl[r] = d.sh[r] >> 16;               // bf16 pair (s, 0)
+            if constexpr (SYM) {
+                d.c[r] = s * -136.0f;
+            } else {
+                float p;                           // -z s, scaled as on the matrix-core route (DeqSel)
+                asm("v_fma_mix_f32 %0, %1, %1, 0 op_sel:[0,1,0] op_sel_hi:[1,1,0]" : "=v"(p) : "v"(v[r]));
+                d.c[r] = __builtin_fmaf(p, kF16Unscale, s * -128.0f);   // -(128 + z) * s, exactly
+            }
+        }
+        return d;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        d.c[r] = dot2(sz[r], sz[r] >> 16, 0.0f);   // -(128 + z) * s
-        d.sl[r] = sz[r] & 0xFFFFu;   // bf16 pair (s, 0)
-        d.sh[r] = sz[r] << 16;       // bf16 pair (0, s)
+        const uint32_t sz = SYM ? (((r & 1) ? v[r] >> 16 : v[r] & 0xFFFFu) | (kZcSymmetric << 16)) : v[r];
+        d.c[r] = dot2(sz, sz >> 16, 0.0f);   // -(128 + z) * s
+        d.sl[r] = sz & 0xFFFFu;      // bf16 pair (s, 0)
+        d.sh[r] = sz << 16;          // bf16 pair (0, s)
     }
     return d;
-}
-
-// The bf16 word s | zc << 16 of column r of a 4-column block from what a
-// handle stores for it (v = the 32-bit word, or for symmetric handles the 16
-// bits in the half of the column's parity).  The scale comes out itself, whatever
-// the route: the vector unit flushes binary32's subnormals, so scaled sums would
-// vanish 2^12 earlier.
-template <bool SYM>
-__device__ inline uint32_t valu_word(uint32_t v, int r, bool f16) {
-    const uint32_t own = (r & 1) ? v >> 16 : v & 0xFFFFu, other = (r & 1) ? v & 0xFFFFu : v >> 16;
-    if (f16) {
-        const float s = (float)__builtin_bit_cast(_Float16, (uint16_t)own) *
-                        __builtin_ldexpf(1.0f, r >= 2 ? 4 - kF16Exp : -kF16Exp);
-        const uint32_t z = SYM ? 8u : (other & 0x7FFFu) >> (r >= 2 ? 4 : 0);
-        return (__float_as_uint(s) >> 16) | ((0xC300u | z) << 16);
-    }
-    return SYM ? (own | (kZcSymmetric << 16)) : v;
 }
 
 // Dequantize one packed word: pr[r] = bf16 pair (w[n_r][k0], w[n_r][k0 + 4]) with

@@ -154,8 +154,8 @@ __global__ void k_dequant_valu(const uint4 *__restrict__ codes, const void *__re
          b += (size_t)gridDim.x * (blockDim.x >> 6)) {
         const uint4 c = codes[b * 64 + l];
         uint32_t s4[4];
-        for (int r = 0; r < 4; ++r) s4[r] = valu_word<SYM>(load_sz<SYM>(sz, b, 4 * b2 + r), r, f16);
-        const ValuDeq d = valu_setup(s4);
+        for (int r = 0; r < 4; ++r) s4[r] = load_sz<SYM>(sz, b, 4 * b2 + r);
+        const ValuDeq d = valu_setup<SYM>(s4, f16);
         const uint32_t P[4] = {c.x, c.y, c.z, c.w};
         const int t = (int)(b / Kb), kb = (int)(b % Kb);
         for (int j = 0; j < 4; ++j) {
@@ -485,15 +485,15 @@ struct GemvGroup {
     uint32_t x[MV][4];
 };
 
-template <int MV, int TN, bool SYM, Route R>
+template <int MV, int TN, bool SYM>
 __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float *slots = (float *)smem;                  // [kWaves][TN][MV][16]
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const ExtractConsts<false> kx;
-    WgWork w = wg_work<R>(a, blockIdx.x);
-    w.unscale = 1.0f;                              // valu_word() does not scale
+    WgWork w = wg_work<kRouteMixed>(a, blockIdx.x);
+    w.unscale = 1.0f;                              // valu_setup() does not scale
     const int Tn = w.Tn;
     int u0, u1;
     wave_range(Tn * w.Kc, wave, u0, u1);
@@ -508,7 +508,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[t][m][r] = 0.0f;
 
-    if (u0 < u1) {
+    auto walk = [&](auto route) {
         WaveGroups wg;
         wg.init(u0, u1, Tn);
         auto load_group = [&](GemvGroup<MV, TN> &B, int kbl) {
@@ -520,7 +520,7 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
                 B.c[t] = load_block_nt(w.codes, b * 64 + lane);
                 if constexpr (SYM) {
                     const uint2 h = __builtin_bit_cast(uint2, __builtin_nontemporal_load((const v2u *)((const uint16_t *)w.sz + b * kTileN + 4 * b2)));
-                    B.s[t] = make_uint4(h.x, h.x, h.y, h.y);       // valu_word picks the column's half
+                    B.s[t] = make_uint4(h.x, h.x, h.y, h.y);       // valu_setup picks the column's half
                 } else {
                     B.s[t] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const v4u *)((const uint32_t *)w.sz + b * kTileN + 4 * b2)));
                 }
@@ -540,9 +540,8 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
 #pragma unroll
             for (int t = 0; t < TN; ++t) {
                 if (t >= ta && t < tb) {
-                    const uint32_t s4[4] = {valu_word<SYM>(B.s[t].x, 0, w.f16), valu_word<SYM>(B.s[t].y, 1, w.f16),
-                                            valu_word<SYM>(B.s[t].z, 2, w.f16), valu_word<SYM>(B.s[t].w, 3, w.f16)};
-                    const ValuDeq d = valu_setup(s4);
+                    const uint32_t s4[4] = {B.s[t].x, B.s[t].y, B.s[t].z, B.s[t].w};
+                    const ValuDeq d = valu_setup<SYM>(s4, decltype(route)::value);
                     const uint32_t P[4] = {B.c[t].x, B.c[t].y, B.c[t].z, B.c[t].w};
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -558,7 +557,8 @@ __global__ void __launch_bounds__(kThreads) k_gemv4(FwdArgs a) {
         };
         GemvGroup<MV, TN> ring[ring_groups<TN>()];
         group_ring(wg.kg0, wg.kg1, ring, load_group, compute_group);
-    }
+    };
+    if (u0 < u1) on_route<kRouteMixed>(w.f16, walk);
     // sum over the 16 lanes sharing b2 (lane bits 0, 1, 4, 5), then one lane per b2 writes
 #pragma unroll
     for (int t = 0; t < TN; ++t) {
@@ -795,10 +795,10 @@ static FwdKernel pick_regs(int kern, int mrows) {
     if (kern == kKernMfma16) return k_mfma16<TN, SYM, R>;
     if constexpr (TN <= kTnMaxGemv) {
         switch (mrows) {
-            case 1: return k_gemv4<1, TN, SYM, R>;
-            case 2: return k_gemv4<2, TN, SYM, R>;
-            case 3: return k_gemv4<3, TN, SYM, R>;
-            case 4: return k_gemv4<4, TN, SYM, R>;
+            case 1: return k_gemv4<1, TN, SYM>;     // any route
+            case 2: return k_gemv4<2, TN, SYM>;
+            case 3: return k_gemv4<3, TN, SYM>;
+            case 4: return k_gemv4<4, TN, SYM>;
         }
     }
     return nullptr;
