@@ -1,6 +1,7 @@
-// Device-side building blocks shared by the forward kernels (kernels.hip,
-// tiled.hip): vector types, the block layout, the nibble extraction and the
-// two exact dequantization routes.  Header-only, inline.
+// Device-side building blocks shared by the kernels (kernels.hip, mid.hip,
+// tiled.hip and, for its vector types and cross-lane helpers, attn.hip): vector
+// types, the block layout, the nibble extraction and the two exact
+// dequantization routes.  Header-only, inline.
 #pragma once
 
 #include "qlin_internal.h"

@@ -477,7 +477,11 @@ __global__ void __launch_bounds__(kThreads) k_mfma16(FwdArgs a) {
 //
 // Same walk as k_mfma16.  Lane l (b2 = (l >> 2) & 3, g = l >> 4, i = l & 3)
 // holds, for every row m and step j, the bf16 pair (x[m][k], x[m][k + 4]) with
-// k = 128 kb + 32 j + 8 g + i, matching valu_dequant()'s weight pairs.
+// k = 128 kb + 32 j + 8 g + i, matching valu_dequant()'s weight pairs.  The
+// stored scales of either route give the same unscaled constants, so one kernel
+// serves both.  Forced only: the vector products bound it, 9728 x 2560 at 1 / 4
+// rows takes 11.0 / 17.9 us (6.4 at one row by the automatic plan; 11.4 / 18.4
+// with the f16 route's scales turned back into bf16 words first).
 template <int MV, int TN>
 struct GemvGroup {
     uint4 c[TN];

@@ -46,17 +46,17 @@ struct XLoads {
 // Measured (graph replays over rotating weights, us a launch; before: the
 // staged kernel of 16 rows and fewer with up to four m-tiles, whose x chunk
 // fitted LDS only for K splits of 5 to 26): 2560 x 19456 at 32 / 48 / 64 rows
-// 12.5 / 14.6 / 16.7 (34 / 35 / 60 before, 17.4 / 17.6 / 18.1 as 64 x 128
-// blocks of the tiled kernel), 9728 x 2560 10.3 / 12.3 / 13.9 (21 / 22 / 37;
-// tiled 16.6 / 16.7 / 17.0).  Of the 16.7 us, 8.2 go to the loads (every
-// workgroup reads all of x, 327 KB, mostly from L2, beside its weights), 3.3
-// to products that the loads do not cover, 2.4 to the sums in LDS and 1.4 to
-// the stores.  Requesting the weights two rounds ahead (two copies of the
+// 12.9 / 14.5 / 16.8 (34 / 35 / 61 before, 17.6 / 18.4 / 18.5 as 64 x 128
+// blocks of the tiled kernel), 9728 x 2560 10.9 / 12.4 / 14.0 (21 / 22 / 37;
+// tiled 16.4 / 16.6 / 16.7).  At 64 rows of 2560 x 19456 half of the time goes
+// to the loads (every workgroup reads all of x, 327 KB, mostly from L2, beside
+// its weights), a fifth to products that the loads do not cover and a quarter
+// to the sums and stores.  Requesting the weights two rounds ahead (two copies of the
 // walk's body) was 0.6 to 1.4 us slower; a workgroup-wide pipeline of 4-group
 // steps, two waves a group, with a barrier a step took 15.3 us at 32 rows.
 // Beyond 64 rows, against the tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows
-// 10.9 / 12.8 / 15.4 (14.1 / 14.1 / 17.0), 2560 x 12288 at 65 / 90 rows
-// 13.3 / 15.4 (17.1 / 17.1), 512 x 2048 at 65 / 128 rows 4.3 / 5.2 (5.7 / 5.9).
+// 10.8 / 12.8 / 14.9 (14.1 / 14.1 / 17.1), 2560 x 12288 at 65 / 90 rows
+// 13.3 / 15.5 (17.7 / 18.0), 512 x 2048 at 65 / 128 rows 4.3 / 5.2 (5.9 / 5.9).
 //
 // At the end the waves' sums are added in LDS in a fixed order: wave w + 4 to
 // wave w, then the four sums in order; of a single round of groups shared by tile

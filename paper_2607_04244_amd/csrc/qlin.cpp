@@ -36,7 +36,8 @@ struct qlin_s {
     size_t ws_bytes = 0;
     int cap_rows = 0;            // S * M the full workspace capacity covers (depends on K only)
     // the automatic plans for M = 1 .. 64 with the handle's workspace,
-    // computed at creation (qlin_forward then plans nothing per call)
+    // computed at creation: qlin_forward looks nothing up there.  Groups, forced
+    // plans, more rows and a caller's workspace go by the thread's memory (plan_for).
     CachedPlan *auto_plans = nullptr;
 };
 
@@ -155,11 +156,12 @@ int check_zeros(const uint16_t *z, size_t n) {
     return QLIN_OK;
 }
 
-// Does a K chunk of Kc groups fit one SKINNY workgroup with M rows (staged x
-// + one column tile)?
+// Does a K chunk of Kc groups fit LDS with M rows (staged x + one column tile)?
+// At M <= 16 this is the need of k_skinny; above it is the limit that a forced
+// split has, whose K chunks k_mid does not keep in LDS.
 bool chunk_fits(int M, int Kc) { return lds_bytes(M, Kc, 1) <= kLdsMax; }
 
-// Smallest number of K chunks whose chunks fit a SKINNY workgroup.
+// Smallest number of K chunks whose chunks fit by that rule.
 int min_split(int M, int Kb) {
     for (int S = 1; S <= Kb; ++S)
         if (chunk_fits(M, (Kb + S - 1) / S)) return S;
@@ -198,8 +200,8 @@ struct Plan {
     int counters = 0;  // arrival counters it uses (K split)
 };
 
-// S * M the full capacity covers for K = 128 Kb: the larger of 128 and the
-// smallest feasible split of a 64-row chunk times its rows.
+// S * M the full capacity covers for K = 128 Kb: the larger of 128 and, over
+// M = 1 .. 64, M times the smallest split whose chunks fit (min_split).
 int capacity_rows(int Kb) {
     int rows = kCapRowsMin;
     for (int M = 1; M <= kMaxSkinnyM; ++M) {
@@ -319,7 +321,7 @@ int gemv_max_auto() {
 // Estimated time (ns) of a k_mid launch: rounds of 8 groups, each with the x of
 // the waves and the blocks of the tiles, or, if longer, the x of all workgroups
 // at the 15.8 TB/s their L2s give; per tile the sums at the end; for a split the
-// trips of the partial sums.  Fitted to 1900 launches at 17, 32, 48 and 64 rows of
+// trips of the partial sums.  Fitted to 1970 launches at 17, 32, 48 and 64 rows of
 // K = 1024 to 9728 and N = 256 to 24576 in 1 to 16 chunks (9% root mean square);
 // over the 356 shapes among them the split it chooses is on average 0.5% slower
 // than the fastest one timed, and at most 18% (2048 x 256 at 64 rows).
@@ -643,8 +645,8 @@ int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p
 // a K split its chunks and partial blocks.  Of 1320 choices timed there one came
 // out more than 3 % slower than the tiled plan (5 %) and 987 faster; on average a
 // choice is 0.1 % slower than the better kernel.  Measured, k_mid against the
-// tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows 10.8 / 12.9 / 15.4 us against
-// 14.3 / 14.4 / 17.3, 640 x 208 at 144 rows 5.0 against 6.0; 9728 x 3872 at 144
+// tiled kernel: 2560 x 6144 at 65 / 96 / 129 rows 10.8 / 12.8 / 14.9 us against
+// 14.1 / 14.1 / 17.1, 640 x 208 at 144 rows 5.0 against 6.0; 9728 x 3872 at 144
 // rows 38.6 against 30.7, 2944 x 2560 at 144 rows 14.4 against 12.1 (both tiled);
 // past 144 rows x no longer fits LDS.
 bool make_mid_plan(const Target &t, int64_t M, const Plan &q, Plan *p) {
@@ -693,7 +695,8 @@ int make_plan(const Target &t, int path, int64_t split_k, int64_t M, Plan *p) {
 // make_plan with a memory of the calling thread's last plans.  A plan depends
 // on nothing but the numbers in the key, so an entry never goes stale; the
 // search it saves took 11 us of a 16 us grouped call (q|k|v at 16 rows).  64
-// entries a thread (under 30 KiB), each replaced by the next key that hashes to it.
+// entries a thread (under 30 KiB), each replaced by the next key that hashes to
+// it: calls in turn whose keys share an entry pay the search every time.
 struct PlanKey {
     int64_t K, M, split_k;
     uint64_t cap_floats;

@@ -33,7 +33,7 @@ enum Kern {
     kKernGemv = 0,     // k_gemv4: M <= 4, group-major walk, x in registers (GEMV path)
     kKernMfma16 = 1,   // k_mfma16: M <= 16, group-major walk, x in registers (REGS path)
     kKernStaged = 2,   // k_skinny: M <= 16, tile-major walk, x chunk staged in LDS (SKINNY path)
-    kKernMid = 4,      // k_mid<MT, TN>: 17 <= M <= 144, K cut over the waves (SKINNY path, AUTO above 64 rows)
+    kKernMid = 4,      // k_mid<MT, TN>: 17 <= M <= 144, K cut over the waves (SKINNY and AUTO to 64 rows, AUTO above)
     kKernTiled = 3     // k_tiled: any M, 128 x 256 output blocks, x and weights staged in LDS (TILED path)
 };
 
@@ -141,8 +141,10 @@ struct TiledArgs {
 // 19456 at 200 rows 12.5 -> 12.8 us).
 static_assert(offsetof(TiledArgs, gb0) == 64 && offsetof(TiledArgs, mem) == 96 && sizeof(TiledMember) == 32, "");
 
-// Rows of x a SKINNY workgroup keeps in LDS for M rows (M <= 64): the next
-// power of two >= M up to 16, else whole m-tiles of 16.
+// Rows of x a k_skinny workgroup keeps in LDS for M rows: the next power of
+// two >= M.  Above 16 rows, where k_mid runs and keeps no x chunk, whole m-tiles
+// of 16: the limits of forced splits and the capacity of a workspace (min_split,
+// capacity_rows in qlin.cpp) are those of a chunk of that many rows.
 inline int staged_rows(int M) {
     if (M > 16) return 16 * ((M + 15) / 16);
     int r = 1;
@@ -154,7 +156,7 @@ inline int staged_rows(int M) {
 // rows x 16 fp32 per (wave, tile).
 inline size_t lds_bytes_regs(int rows, int tn) { return (size_t)kWaves * tn * rows * 16 * 4; }
 
-// LDS bytes of a SKINNY workgroup with M rows: the x chunk of Kc groups
+// LDS bytes of a k_skinny workgroup with M rows: the x chunk of Kc groups
 // (staged_rows(M) rows of 16 Kc + 1 slots of 16 bytes, in whole 1 KiB
 // direct-to-LDS loads) plus one
 // partial-sum slot (16 m-columns per m-tile x 16 fp32) per (wave, column

@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(kTiledWaves * WS * 64, MSW * NT <= 8 ? 2 : 1) 
         blk = jn * a.Mt + im;
     }
     // the member owning column block jn (every index of the argument arrays
-    // static but one, see wg_work in kernels.hip) and its tiles [t0, t0 + 4 NT)
+    // static but one, see wg_work in decode_common.h) and its tiles [t0, t0 + 4 NT)
     int m = 0, gb = 0;
 #pragma unroll
     for (int i = 1; i < kMaxMembers; ++i)
