@@ -521,7 +521,8 @@ bool auto_tiled(int64_t M) { return M > kMaxSkinnyM; }
 
 // Decode-kernel plan (M <= 64) for the target.  The automatic choice (AUTO)
 // searches the kernel families and K splits that fit LDS and the workspace;
-// 17 .. 64 rows run as k_mid, which needs neither a split nor a workspace.
+// 17 .. 64 rows run as k_mid, which needs neither a split nor a workspace (make_plan
+// gives very wide layers to the tiled kernel).
 int make_decode_plan(const Target &t, int path, int64_t split_k, int Mi, Plan *p) {
     const bool auto_pick = path == kAuto;
     if (path == kAuto) path = (Mi <= gemv_max_auto()) ? kGemv : kSkinny;
@@ -678,8 +679,9 @@ bool make_mid_plan(const Target &t, int64_t M, const Plan &q, Plan *p) {
 }
 
 // The plan of a launch of M rows: TILED (forced, or AUTO above 64 rows, where
-// k_mid may replace it) is one launch over all members; the decode kernels cover all members
-// in one launch per slice of p->rows rows.
+// k_mid may replace it, and for very wide layers from 17 rows on) is one launch
+// over all members; the decode kernels cover all members in one launch per slice
+// of p->rows rows.
 int make_plan(const Target &t, int path, int64_t split_k, int64_t M, Plan *p) {
     if (path < kAuto || path > kRegs) return fail(QLIN_ERR_INVALID, "unknown path %d", path);
     if (split_k < 0 || split_k > t.Kb) return fail(QLIN_ERR_INVALID, "split_k must be in [0, K/128]");
@@ -689,7 +691,22 @@ int make_plan(const Target &t, int path, int64_t split_k, int64_t M, Plan *p) {
         if (rc == QLIN_OK && path == kAuto && split_k == 0 && p->rows == M && make_mid_plan(t, M, *p, &mid)) *p = mid;
         return rc;
     }
-    return make_decode_plan(t, path, split_k, (int)std::min<int64_t>(M, kMaxSkinnyM), p);
+    const int rc = make_decode_plan(t, path, split_k, (int)std::min<int64_t>(M, kMaxSkinnyM), p);
+    // 17 to 64 rows over more columns than the tiles of one round of workgroups:
+    // the tiled kernel, whose 64 x 128 blocks then come in fewer rounds (always,
+    // where they fit one), or in as many over up to 20 groups.  Over 308
+    // shapes of 20496 to 151936 columns the kernel chosen is at most 0.9% slower
+    // than the other and takes on average 0.74 of k_mid's time.  k_mid against
+    // tiled, us: 2560 x 24576 at 64 rows 28.8 / 18.6, 2560 x 49152 at 17 rows 30.2
+    // / 30.3; of as many rounds and 32 groups, 4096 x 49152 at 17 rows 40.1 / 46.0.
+    if (rc == QLIN_OK && path == kAuto && split_k == 0 && p->kern == kKernMid && p->grid > t.num_cu) {
+        auto rounds = [&](int64_t n) { return (n + t.num_cu - 1) / t.num_cu; };
+        Plan q;
+        if (make_tiled_plan(t, 0, M, &q) != QLIN_OK || q.rows != M) return rc;
+        const int64_t work = (int64_t)q.Gn * ((M + q.mrows - 1) / q.mrows) * q.S;
+        if (rounds(work) < rounds(p->grid) || (rounds(work) == rounds(p->grid) && t.Kb <= 20)) *p = q;
+    }
+    return rc;
 }
 
 // make_plan with a memory of the calling thread's last plans.  A plan depends
@@ -1050,6 +1067,7 @@ int run_forward(qlin_s *h, int path, int64_t split_k, int64_t M, const uint16_t 
     const hipStream_t st = (hipStream_t)stream;
     const CachedPlan *cp = (path == kAuto && split_k == 0 && M <= kMaxSkinnyM) ? &h->auto_plans[M - 1] : nullptr;
     if (cp && cp->ok && cp->p.rows >= M) {     // the automatic plan, computed at creation: one launch
+        if (cp->p.kern == kKernTiled) return launch_tiled_rows(t, cp->p, M, x, ys, h->ws, h->ws_bytes, st);
         const FwdArgs a = fwd_args(t, cp->p, M, x, ys, h->ws, h->ws_bytes, 0);
         const hipError_t e = launch_forward(cp->p.kern, cp->p.mrows, cp->p.tn, t.symmetric, route_of(t), cp->p.grid,
                                             cp->p.lds, a, st);

@@ -48,6 +48,26 @@ def test_last_groups_shared_by_tile(M, Kb, N):
     lin.close()
 
 
+@pytest.mark.parametrize("M,K,Ns", [(17, 128, (32784,)), (48, 256, (24592,)), (49, 384, (20480, 16)),
+                                    (64, 512, (11280, 9232))])
+def test_very_wide_layers_run_as_tiled_blocks(M, K, Ns):
+    """More columns than one round of workgroups holds: the tiled kernel, from a
+    handle's own plans and for a group."""
+    cs = [gen.random_case(M + K + N, M, K, N) for N in Ns]
+    lins = [make(c) for c in cs]
+    _, plan = qlin.group_plan(lins, M)
+    assert "kernel=k_tiled" in plan or torch.cuda.get_device_properties(0).multi_processor_count != 256, plan
+    if len(Ns) == 1:
+        assert lins[0].plan(M) == plan
+        ys = [run(lins[0], cs[0]["x"])]
+    else:
+        ys = [host_bits(y) for y in qlin.forward_group(lins, dev(cs[0]["x"]))]
+    for y, c in zip(ys, cs):
+        assert_close(y, oracle(dict(c, x=cs[0]["x"])), f"M={M} K={K} N={Ns}")
+    for lin in lins:
+        lin.close()
+
+
 @pytest.mark.parametrize("M", [65, 80, 81, 96, 97, 112, 113, 128, 129, 144])
 @pytest.mark.parametrize("Kb,N", [(3, 48), (4, 16), (5, 208), (9, 224), (13, 4112)])
 def test_half_group_units_end_unevenly(M, Kb, N):

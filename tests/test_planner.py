@@ -53,8 +53,8 @@ def plan(lib, Ns, K, M, path=AUTO, split=0, ws=-1, symmetric=False):
 
 
 @pytest.mark.parametrize("Ns,K,M,path,split", [
-    ([1 << 20] * 8, 128, 64, AUTO, 0),         # over 100000 ranges, no K split
-    ([1048512] * 8, 128, 48, AUTO, 0),
+    ([1 << 20] * 8, 128, 64, SKINNY, 0),       # over 100000 ranges, no K split
+    ([1048512] * 8, 128, 48, SKINNY, 0),
     ([1 << 20], 128, 64, SKINNY, 0),
     ([1 << 20] * 8, 256, 16, AUTO, 0),
     ([1 << 20] * 8, 128, 16, REGS, 0),
@@ -134,6 +134,24 @@ def test_splits_at_17_to_64_rows(planner, M, K, N, chunks):
 
 
 TILED_KERNEL, MID_KERNEL = 3, 4
+
+
+@pytest.mark.parametrize("M,K,Ns,kern", [
+    (64, 2560, [20480], MID_KERNEL), (64, 2560, [20496], TILED_KERNEL), (64, 2560, [24576], TILED_KERNEL),
+    (49, 640, [22000], TILED_KERNEL), (48, 2560, [24576], MID_KERNEL), (48, 2560, [24592], TILED_KERNEL),
+    (17, 2560, [32768], MID_KERNEL), (17, 512, [65552], TILED_KERNEL), (32, 1024, [40960, 8192], TILED_KERNEL),
+    (64, 4096, [41200], TILED_KERNEL), (64, 2560, [151936], TILED_KERNEL), (17, 4096, [49152], MID_KERNEL),
+    (33, 9728, [32784], MID_KERNEL), (64, 128, [24576], TILED_KERNEL),
+])
+def test_kernel_of_very_wide_layers_at_17_to_64_rows(planner, M, K, Ns, kern):
+    """The faster kernel where both were timed and a workgroup each does not hold
+    all columns (2560 x 20496 at 64 rows: 26.8 us in two rounds of k_mid, 17.9 as
+    161 tiled blocks), without scratch and for any of it."""
+    for ws in (-1, 0, 16 << 20):
+        rc, p = plan(planner, Ns, K, M, ws=ws)
+        assert rc == qlin.QLIN_OK and (p.kern, p.S, p.ws_bytes, p.rows) == (kern, 1, 0, M), (ws, p.kern, p.S)
+    rc, p = plan(planner, Ns, K, M, path=SKINNY)      # forced, the path's own kernel
+    assert rc == qlin.QLIN_OK and p.kern == MID_KERNEL
 
 
 @pytest.mark.parametrize("M,K,N,ws,kern", [
