@@ -35,7 +35,11 @@ struct XLoads {
 // (128 k) up to 64 rows and half a group beyond, where the x of a whole one
 // would take 32 MT of a lane's registers.  With whole groups a last round of
 // up to four gives each to two waves, 64 k each; where it is the only round they
-// load no more than they use: every other tile each or, of one tile, 64 k.
+// load no more than they use: every other tile each or, of one tile, 64 k.  Of
+// five or six groups in the only round the last ones are divided by tiles over waves
+// 4 to 7, as each of these shares a SIMD with one of the first four: 640 x 19456 at
+// 17 / 32 / 48 rows 6.8 / 7.1 / 7.9 -> 6.1 / 6.45 / 7.2 us, 768 x 16384 6.2 / 6.45 /
+// 7.1 -> 5.8 / 6.1 / 6.9 (seven divided that way were 3 to 7% slower).
 //
 // The waves share nothing before the end: a wave stages its unit's x in LDS
 // of its own with direct-to-LDS loads (LDS only turns rows into operand
@@ -89,10 +93,23 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     const int units = HG ? 2 * w.Kc : w.Kc;
     const int full = units / kWaves, rem = units % kWaves;
     const bool paired = !HG && rem <= kHalf;
-    const int tail = paired ? wave >> 1 : wave;      // its unit among the last ones
+    const bool alone = kShareTiles && full == 0 && rem < 7;   // one round of shared groups is all
+    // the unit of a wave in it, and its tiles t, with (t & mask) == pick: up to four
+    // groups by pairs of waves; of five or six, one each to waves 0 .. 3 and the
+    // rest divided over waves 4 .. 7, each on a SIMD with one of the first
+    struct Part1 {
+        int unit, mask, pick;
+    };
+    auto part_of = [&](int wv) -> Part1 {
+        if (rem <= kHalf) return {wv >> 1, 1, wv & 1};
+        if (wv < kHalf) return {wv, 0, 0};
+        if (rem == 5) return {4, 3, wv & 3};
+        return {4 + (wv & 1), 1, wv >> 1 & 1};
+    };
+    const Part1 part = part_of(wave);
+    const int tail = alone ? part.unit : paired ? wave >> 1 : wave;   // its unit among the last ones
     const int last = tail < rem ? 1 : 0;             // takes part in the last round
-    const bool alone = paired && full == 0;          // one round of shared groups is all
-    auto other = [&](int t) { return ((t ^ wave) & 1) != 0; };   // a tile of the other wave of its pair
+    auto other = [&](int t) { return (t & part.mask) != part.pick; };   // a tile of another wave
     auto group_of = [&](int u) { return HG ? u >> 1 : u; };
     auto half_of = [&](int u) { return HG ? (uint32_t)(u & 1) : 0u; };
 
@@ -260,13 +277,33 @@ __global__ void __launch_bounds__(kThreads) k_mid(FwdArgs a) {
     auto at = [&](int set, int t, int mt) {
         return (v4f *)(sums + (size_t)(set * TN + t) * ROWS * 16 + 4 * sums_unit(16 * mt + lm, lg));
     };
-    if (kShareTiles && alone) {
+    if (alone && rem <= kHalf) {
         // one round of shared groups: the pairs are the sets, each tile in one wave of a pair
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
                 if (t < w.Tn && !other(t)) *at(wave >> 1, t, mt) = acc[t][mt];
+    } else if (alone) {
+        // five or six groups: wave w + 4, in the tiles it has, to wave w
+        const Part1 partner = part_of(wave | kHalf);
+        const int set = wave & (kHalf - 1);
+        if (wave >= kHalf) {
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    if (t < w.Tn && !other(t)) *at(set, t, mt) = acc[t][mt];
+        }
+        lds_barrier();
+        if (wave < kHalf) {
+#pragma unroll
+            for (int t = 0; t < TN; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    if (t < w.Tn)
+                        *at(set, t, mt) = (t & partner.mask) == partner.pick ? acc[t][mt] + *at(set, t, mt) : acc[t][mt];
+        }
     } else {
         // wave w + 4 to wave w (no sums in waves past the last unit of a single round)
         auto busy = [&](int wv) { return full > 0 || (paired ? wv >> 1 : wv) < rem; };

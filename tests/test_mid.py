@@ -36,12 +36,12 @@ def test_rounds_tiles_and_rows_end_unevenly(M, Kb, N):
 
 
 @pytest.mark.parametrize("M", [17, 48, 64])
-@pytest.mark.parametrize("Kb,N", [(1, 8208), (2, 12304), (4, 19456), (5, 8192), (7, 12288), (8, 8208), (11, 8208),
-                                  (12, 4112)])
+@pytest.mark.parametrize("Kb,N", [(1, 8208), (2, 12304), (4, 19456), (5, 4112), (5, 8192), (5, 20480), (6, 8208),
+                                  (6, 16400), (7, 12288), (7, 20480), (8, 8208), (11, 8208), (12, 4112)])
 def test_last_groups_shared_by_tile(M, Kb, N):
     """Two and more tiles a workgroup: the waves of a pair take every other tile
-    of a shared last group, alone (up to 4 groups) or after whole rounds; single
-    rounds with waves that have no group (5 to 7)."""
+    of a shared last group, alone (up to 4 groups) or after whole rounds; of 5 to
+    7 groups in one round the last ones by four, two and two waves."""
     c = gen.random_case(M * 1000 + Kb * 10 + N, M, 128 * Kb, N)
     lin = make(c)
     assert_close(run(lin, c["x"], SKINNY), oracle(c), f"M={M} Kb={Kb} N={N}")
